@@ -1,0 +1,328 @@
+// decoder.hip -- what lies between the weight products of a decode pass
+// (splice_decoder.h).  The rows of a pass are few and short, so a launch costs
+// more than its bytes: each kernel here takes the place of a chain of
+// elementwise operations over the same rows, rounding exactly where the chain
+// rounds (floating-point contraction is off).
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "decoder_head.hpp"
+#include "splice_decoder.h"
+
+#pragma clang fp contract(off)
+
+namespace {
+
+using namespace splice_dev;
+
+typedef __bf16 bf16x8v_t __attribute__((ext_vector_type(8)));
+typedef float f32x8v_t __attribute__((ext_vector_type(8)));
+
+constexpr int kDecThreads = 256;
+
+__device__ __forceinline__ f32x8v_t load_f32x8(const float *p) { return *reinterpret_cast<const f32x8v_t *>(p); }
+__device__ __forceinline__ f32x8v_t load_bf16x8(const __bf16 *p) {
+    return __builtin_convertvector(*reinterpret_cast<const bf16x8v_t *>(p), f32x8v_t);
+}
+__device__ __forceinline__ void store_bf16x8(__bf16 *p, f32x8v_t v) {
+    *reinterpret_cast<bf16x8v_t *>(p) = __builtin_convertvector(v, bf16x8v_t);
+}
+
+__global__ __launch_bounds__(kDecThreads) void residual_kernel(float *x, const __bf16 *delta, float *sq, int64_t units,
+                                                               int assign) {
+    const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
+    if (u >= units) return;
+    f32x8v_t v = load_bf16x8(delta + 8 * u);
+    if (!assign) v = load_f32x8(x + 8 * u) + v;
+    *reinterpret_cast<f32x8v_t *>(x + 8 * u) = v;
+    *reinterpret_cast<f32x8v_t *>(sq + 8 * u) = v * v;
+}
+
+__global__ __launch_bounds__(kDecThreads) void norm_kernel(const float *x, const float *mean_sq, const __bf16 *gain,
+                                                           __bf16 *h, int rows, int d, float eps, int packed) {
+    const int per = d / 8;
+    const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
+    if (u >= (int64_t)rows * per) return;
+    const int row = (int)(u / per), c = 8 * (int)(u % per);
+    const float r = (float)(1.0 / sqrt((double)(mean_sq[row] + eps)));   // correctly rounded, as the operation's
+    // packed: the head's tile order [d / 32][ceil(rows / 16)][16][32]
+    const int64_t to = packed ? ((int64_t)(c >> 5) * ((rows + 15) / 16) + (row >> 4)) * 512 + (row & 15) * 32 + (c & 31)
+                              : 8 * u;
+    store_bf16x8(h + to, load_f32x8(x + 8 * u) * r * load_bf16x8(gain + c));
+}
+
+struct RopeSteps {
+    int32_t step[SPLICE_MAX_CELLS];
+};
+__global__ __launch_bounds__(kDecThreads) void rope_table_kernel(float2 *tab, const double *pos, RopeSteps st,
+                                                                 int prompt_len, int rows, int half, double theta) {
+    const int e = blockIdx.x * kDecThreads + threadIdx.x;
+    if (e >= rows * half) return;
+    const int row = e / half, i = e % half;
+    const double p = pos ? pos[row] : (double)(prompt_len + max(st.step[row], 0));
+    const float ang = (float)(p * pow(theta, -(double)i * 2.0 / (double)(2 * half)));
+    tab[e] = make_float2(cosf(ang), sinf(ang));
+}
+
+// A unit is four pairs (i, i + D / 2) of one (row, head).
+__global__ __launch_bounds__(kDecThreads) void rope_kernel(__bf16 *q, __bf16 *k, const float2 *tab, int rows, int Hq,
+                                                           int Hkv, int D) {
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    const int half = D / 2, per = half / 4, heads = Hq + Hkv;
+    const int u = blockIdx.x * kDecThreads + threadIdx.x;
+    if (u >= rows * heads * per) return;
+    const int i = 4 * (u % per), item = u / per, row = item / heads, hd = item % heads;
+    __bf16 *p = (hd < Hq ? q + ((size_t)row * Hq + hd) * D : k + ((size_t)row * Hkv + hd - Hq) * D) + i;
+    const f32x4_t x1 = __builtin_convertvector(*reinterpret_cast<const bf16x4_t *>(p), f32x4_t);
+    const f32x4_t x2 = __builtin_convertvector(*reinterpret_cast<const bf16x4_t *>(p + half), f32x4_t);
+    f32x4_t y1, y2;
+    static_for<0, 4>([&](auto j) {
+        const float2 cs = tab[row * half + i + (int)j];
+        const float a = x1[(int)j], b = x2[(int)j];
+        y1[(int)j] = a * cs.x - b * cs.y;
+        y2[(int)j] = b * cs.x + a * cs.y;
+    });
+    *reinterpret_cast<bf16x4_t *>(p) = __builtin_convertvector(y1, bf16x4_t);
+    *reinterpret_cast<bf16x4_t *>(p + half) = __builtin_convertvector(y2, bf16x4_t);
+}
+
+__global__ __launch_bounds__(kDecThreads) void round_kernel(const float *src, __bf16 *dst, int64_t units) {
+    const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
+    if (u < units) store_bf16x8(dst + 8 * u, load_f32x8(src + 8 * u));
+}
+
+__global__ __launch_bounds__(kDecThreads) void silu_kernel(const __bf16 *gate, const __bf16 *up, __bf16 *act,
+                                                           int64_t units) {
+    const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
+    if (u >= units) return;
+    const f32x8v_t g = load_bf16x8(gate + 8 * u), w = load_bf16x8(up + 8 * u);
+    f32x8v_t o;
+    static_for<0, 8>([&](auto i) {
+        const float x = g[(int)i];
+        o[(int)i] = (float)(__bf16)(x / (1.f + expf(-x))) * w[(int)i];
+    });
+    store_bf16x8(act + 8 * u, o);
+}
+
+// ---------------------------------------------------------------- argmax
+
+// Orders floats as unsigned words, NaN above everything, -0 as 0; the low word
+// makes the lower index the larger key.
+__device__ __forceinline__ uint64_t max_key(float x, int i) {
+    uint32_t u = __float_as_uint(x == 0.f ? 0.f : x);
+    u = x != x ? 0xffffffffu : ((u >> 31) ? ~u : u | 0x80000000u);
+    return ((uint64_t)u << 32) | (uint32_t)~i;
+}
+
+__device__ __forceinline__ uint64_t block_max(uint64_t k) {
+    __shared__ uint64_t s_k[kDecThreads / 64];
+    for (int o = 32; o > 0; o >>= 1) {
+        const uint64_t y = __shfl_xor((unsigned long long)k, o);
+        k = y > k ? y : k;
+    }
+    if ((threadIdx.x & 63) == 0) s_k[threadIdx.x >> 6] = k;
+    __syncthreads();
+    for (int w = 0; w < kDecThreads / 64; ++w) k = s_k[w] > k ? s_k[w] : k;
+    return k;
+}
+
+__global__ __launch_bounds__(kDecThreads) void argmax_part_kernel(const float *logits, int vocab, uint64_t *keys) {
+    const int row = blockIdx.y, parts = gridDim.x;
+    const int per = (vocab + parts - 1) / parts, b = blockIdx.x * per, e = min(b + per, vocab);
+    const float *r = logits + (size_t)row * vocab;
+    uint64_t k = 0;
+    for (int i = b + threadIdx.x; i < e; i += 4 * kDecThreads) {
+        float x[4];
+        static_for<0, 4>([&](auto j) { x[(int)j] = r[min(i + (int)j * kDecThreads, e - 1)]; });
+        static_for<0, 4>([&](auto j) {
+            const uint64_t y = max_key(x[(int)j], min(i + (int)j * kDecThreads, e - 1));
+            k = y > k ? y : k;
+        });
+    }
+    k = block_max(k);
+    if (threadIdx.x == 0) keys[(size_t)row * parts + blockIdx.x] = k;
+}
+
+__global__ __launch_bounds__(kDecThreads) void argmax_kernel(const uint64_t *keys, int parts, int64_t *tokens) {
+    const uint64_t k = block_max((int)threadIdx.x < parts ? keys[(size_t)blockIdx.x * parts + threadIdx.x] : 0);
+    if (threadIdx.x == 0) tokens[blockIdx.x] = (int64_t)(uint32_t)~(uint32_t)k;
+}
+
+// ---------------------------------------------------------------- host side
+
+unsigned blocks_of(int64_t units) { return (unsigned)((units + kDecThreads - 1) / kDecThreads); }
+
+constexpr int64_t kMostValues = (int64_t)1 << 38;   // the grid of eight values a thread stays below 2^31 blocks
+
+bool good(std::initializer_list<const void *> ptrs) {
+    for (const void *p : ptrs)
+        if (!p || !splice::aligned(p, 16)) return false;
+    return true;
+}
+
+// How the columns of a head are spread: `n_full` whole tiles, the rest split
+// over K.  Tiles run in rounds of as many work groups as the GPU holds; a last
+// round that is at most half full takes as long as a full one, so its tiles
+// are cut over K until they fill it.
+struct HeadPlan {
+    int n_full, split, rest;   // rest: columns that are split
+};
+
+int compute_units() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    return n;
+}
+
+HeadPlan head_plan(int tiles, int cols, int resident, int M, int K, int N) {
+    HeadPlan p{tiles, 1, 0};
+    if (resident < 1 || tiles <= resident || M > 128) return p;
+    const int last = tiles % resident;
+    int split = last > 0 ? resident / last : 1;
+    if (split > K / 512) split = K / 512;   // at least 16 steps each
+    if (split > 8) split = 8;
+    if (split < 2) return p;
+    p.n_full = tiles - last;
+    p.split = split;
+    p.rest = N - p.n_full * cols;
+    return p;
+}
+
+// Up to 16 rows X is a small part of what a work group reads: 128 columns and
+// two work groups a compute unit (8 rows, 151936 columns: 214 us against 220 of
+// 256 columns and one); above, 256 columns (32 rows, 131072 columns: 165 us
+// against 186).
+constexpr int kHeadNarrowRows = 16;
+constexpr int kHeadWide = 256;
+
+template <int MB, int NS, int NB, int WN, int WM>
+void launch_head(HeadArgs a, const HeadPlan &p, float *part, hipStream_t stream) {
+    using X = Head<MB, NS, NB, WN, WM>;
+    a.n_full = p.n_full;
+    a.split = p.split;
+    a.part = part;
+    const int tiles = (a.N + X::COLS - 1) / X::COLS;
+    const dim3 grid((unsigned)(p.n_full + (tiles - p.n_full) * p.split), (unsigned)((a.M + 16 * MB - 1) / (16 * MB)));
+    hipLaunchKernelGGL((head_kernel<MB, NS, NB, WN, WM>), grid, dim3(64 * WN * WM), 0, stream, a);
+    if (p.rest > 0)
+        hipLaunchKernelGGL(head_sum_kernel, dim3((unsigned)(((int64_t)a.M * p.rest / 4 + 255) / 256)), dim3(256), 0, stream,
+                           part, a.y, a.M, a.N, a.N - p.rest, p.split);
+}
+
+HeadPlan plan_of(int rows, int d, int vocab) {
+    if (rows <= kHeadNarrowRows) return HeadPlan{(vocab + 127) / 128, 1, 0};
+    return head_plan((vocab + kHeadWide - 1) / kHeadWide, kHeadWide, compute_units(), rows, d, vocab);
+}
+
+int32_t launched() { return hipGetLastError() == hipSuccess ? SPLICE_OK : SPLICE_EHIP; }
+
+}  // namespace
+
+extern "C" {
+
+int32_t splice_decoder_residual(float *x, const void *delta, float *sq, int64_t n, int32_t assign, void *stream) {
+    if (!good({x, delta, sq})) return SPLICE_EINVAL;
+    if (n < 8 || n % 8 || n > kMostValues) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(residual_kernel, dim3(blocks_of(n / 8)), dim3(kDecThreads), 0, (hipStream_t)stream, x,
+                       (const __bf16 *)delta, sq, n / 8, assign);
+    return launched();
+}
+
+int32_t splice_decoder_norm(const float *x, const float *mean_sq, const void *gain, void *h, int32_t rows, int32_t d,
+                            float eps, int32_t packed, void *stream) {
+    if (!good({x, gain, h}) || !mean_sq || !splice::aligned(mean_sq, 4)) return SPLICE_EINVAL;
+    if (rows < 1 || d < 8 || d % 8 || (packed && d % 32)) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(norm_kernel, dim3(blocks_of((int64_t)rows * (d / 8))), dim3(kDecThreads), 0, (hipStream_t)stream,
+                       x, mean_sq, (const __bf16 *)gain, (__bf16 *)h, rows, d, eps,
+                       packed);
+    return launched();
+}
+
+int32_t splice_decoder_rope_table(float *tab, const double *pos, const int32_t *cell_step, int32_t rows,
+                                  int32_t head_dim, int32_t prompt_len, double theta, void *stream) {
+    if (!good({tab}) || (!pos && !cell_step) || (pos && !splice::aligned(pos, 8))) return SPLICE_EINVAL;
+    if (rows < 1 || rows > SPLICE_MAX_CELLS || head_dim < 2 || head_dim % 2 || head_dim > 1024)
+        return SPLICE_EUNSUPPORTED;
+    RopeSteps st;
+    for (int c = 0; c < SPLICE_MAX_CELLS; ++c) st.step[c] = !pos && c < rows ? cell_step[c] : 0;
+    hipLaunchKernelGGL(rope_table_kernel, dim3(blocks_of((int64_t)rows * (head_dim / 2))), dim3(kDecThreads), 0,
+                       (hipStream_t)stream, (float2 *)tab, pos, st, prompt_len, rows, head_dim / 2, theta);
+    return launched();
+}
+
+int32_t splice_decoder_rope(void *q, void *k, const float *tab, int32_t rows, int32_t n_q, int32_t n_kv,
+                            int32_t head_dim, void *stream) {
+    if (!good({q, k, tab})) return SPLICE_EINVAL;
+    if (rows < 1 || n_q < 1 || n_kv < 1 || head_dim < 8 || head_dim % 8 ||
+        (int64_t)rows * ((int64_t)n_q + n_kv) * head_dim > INT32_MAX)
+        return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(rope_kernel, dim3(blocks_of((int64_t)rows * (n_q + n_kv) * (head_dim / 8))), dim3(kDecThreads), 0,
+                       (hipStream_t)stream, (__bf16 *)q, (__bf16 *)k, (const float2 *)tab, rows, n_q, n_kv, head_dim);
+    return launched();
+}
+
+int32_t splice_decoder_round(const float *src, void *dst, int64_t n, void *stream) {
+    if (!good({src, dst})) return SPLICE_EINVAL;
+    if (n < 8 || n % 8 || n > kMostValues) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(round_kernel, dim3(blocks_of(n / 8)), dim3(kDecThreads), 0, (hipStream_t)stream, src,
+                       (__bf16 *)dst, n / 8);
+    return launched();
+}
+
+int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int64_t n, void *stream) {
+    if (!good({gate, up, act})) return SPLICE_EINVAL;
+    if (n < 8 || n % 8 || n > kMostValues) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(silu_kernel, dim3(blocks_of(n / 8)), dim3(kDecThreads), 0, (hipStream_t)stream,
+                       (const __bf16 *)gate, (const __bf16 *)up, (__bf16 *)act, n / 8);
+    return launched();
+}
+
+int64_t splice_decoder_head_bytes(int32_t rows, int32_t d, int32_t vocab) {
+    if (rows < 1 || rows > SPLICE_MAX_CELLS || d < 32 || d % 32 || d > 1 << 20 || vocab < 8 || vocab % 8 ||
+        vocab > 1 << 24)
+        return SPLICE_EUNSUPPORTED;
+    const HeadPlan p = plan_of(rows, d, vocab);
+    return p.rest > 0 ? (int64_t)p.split * rows * p.rest * 4 : 0;
+}
+
+int32_t splice_decoder_head(const void *h, const void *w, float *logits, int32_t rows, int32_t d, int32_t vocab,
+                            void *scratch, size_t scratch_bytes, void *stream) {
+    const int64_t need = splice_decoder_head_bytes(rows, d, vocab);
+    if (need < 0) return (int32_t)need;
+    if (!good({h, w, logits})) return SPLICE_EINVAL;
+    if (need > 0 && (!scratch || !splice::aligned(scratch, 16) || scratch_bytes < (size_t)need)) return SPLICE_EWORKSPACE;
+    const HeadPlan p = plan_of(rows, d, vocab);
+    const HeadArgs a{(const char *)h, (const char *)w, logits, rows, d, vocab, 0, 1, nullptr};
+    hipStream_t st = (hipStream_t)stream;
+    float *part = (float *)scratch;
+    // as many row blocks as there are rows, at most 128 rows a work group (then
+    // the weights are read again)
+    if (rows <= 16) launch_head<1, 2, 8, 4, 1>(a, p, part, st);
+    else if (rows <= 32) launch_head<2, 4, 8, 8, 1>(a, p, part, st);
+    else if (rows <= 64) launch_head<4, 4, 7, 4, 2>(a, p, part, st);
+    else launch_head<8, 4, 6, 4, 2>(a, p, part, st);
+    return launched();
+}
+
+int32_t splice_decoder_argmax(const float *logits, int32_t rows, int32_t vocab, int64_t *tokens, void *scratch,
+                              void *stream) {
+    if (!logits || !tokens || !scratch) return SPLICE_EINVAL;
+    if (rows < 1 || rows > 65535 || vocab < 1 || vocab > 1 << 24) return SPLICE_EUNSUPPORTED;
+    // about eight work groups a compute unit, each with a thousand values or more
+    int parts = (2048 + rows - 1) / rows;
+    const int most = (vocab + 1023) / 1024;
+    parts = parts < most ? parts : most;
+    parts = parts < SPLICE_ARGMAX_PARTS ? parts : SPLICE_ARGMAX_PARTS;
+    hipLaunchKernelGGL(argmax_part_kernel, dim3((unsigned)parts, (unsigned)rows), dim3(kDecThreads), 0,
+                       (hipStream_t)stream, logits, vocab, (uint64_t *)scratch);
+    hipLaunchKernelGGL(argmax_kernel, dim3((unsigned)rows), dim3(kDecThreads), 0, (hipStream_t)stream,
+                       (const uint64_t *)scratch, parts, tokens);
+    return launched();
+}
+
+}  // extern "C"

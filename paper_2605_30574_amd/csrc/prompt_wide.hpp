@@ -100,14 +100,24 @@ __device__ __forceinline__ u32x4_t rows_desc(const char *base, int bytes) {
 // buffers apart, would otherwise wait for every load in flight before each
 // LDS read (s_waitcnt vmcnt(0)) and undo the prefetch; the stream waits on
 // vmcnt itself.  M0 holds the LDS base; the statement declares M0 clobbered,
-// so the compiler keeps nothing in it across the load.
+// so the compiler keeps nothing in it across the load.  NT: non-temporal, for
+// rows that are read once.
+template <bool NT = false>
 __device__ __forceinline__ void lds_dma16(u32x4_t desc, uint32_t lds_addr, int voff) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "buffer_load_dwordx4 %1, %2, 0 offen lds"
-        :
-        : "s"(lds_addr), "v"(voff), "s"(desc)
-        : "memory", "m0");
+    if constexpr (NT)
+        asm volatile(
+            "s_mov_b32 m0, %0\n\t"
+            "buffer_load_dwordx4 %1, %2, 0 offen nt lds"
+            :
+            : "s"(lds_addr), "v"(voff), "s"(desc)
+            : "memory", "m0");
+    else
+        asm volatile(
+            "s_mov_b32 m0, %0\n\t"
+            "buffer_load_dwordx4 %1, %2, 0 offen lds"
+            :
+            : "s"(lds_addr), "v"(voff), "s"(desc)
+            : "memory", "m0");
 }
 
 __device__ __forceinline__ uint32_t lds_offset(const char *p) {

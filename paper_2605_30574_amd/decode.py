@@ -22,12 +22,58 @@ reference in ``oracle.decoder``):
 """
 from __future__ import annotations
 
+import ctypes
 from typing import List, Optional
 
 import numpy as np
 import torch
 
 from . import splice as S
+
+ARGMAX_PARTS = 64   # SPLICE_ARGMAX_PARTS
+_declared = None
+
+
+def _library():
+    """The library with the prototypes of include/splice_decoder.h."""
+    global _declared
+    lib = S.load_library()
+    if _declared is not lib:
+        vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
+        for name, args in (("residual", [vp, vp, vp, i64, i32, vp]),
+                           ("norm", [vp, vp, vp, vp, i32, i32, ctypes.c_float, i32, vp]),
+                           ("rope_table", [vp, vp, vp, i32, i32, i32, ctypes.c_double, vp]),
+                           ("rope", [vp, vp, vp, i32, i32, i32, i32, vp]),
+                           ("round", [vp, vp, i64, vp]), ("silu", [vp, vp, vp, i64, vp]),
+                           ("head", [vp, vp, vp, i32, i32, i32, vp, ctypes.c_size_t, vp]), ("argmax", [vp, i32, i32, vp, vp, vp])):
+            f = getattr(lib, "splice_decoder_" + name)
+            f.restype, f.argtypes = i32, args
+        lib.splice_decoder_head_bytes.restype, lib.splice_decoder_head_bytes.argtypes = i64, [i32, i32, i32]
+        _declared = lib
+    return lib
+
+
+def _plain(t, device, *shape) -> bool:
+    """A bf16 matrix of this shape on the device that autograd does not follow (any strides)."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == torch.bfloat16 and t.device == device and
+            tuple(t.shape) == shape and not (t.requires_grad and torch.is_grad_enabled()))
+
+
+def _dense(t) -> bool:
+    return t.is_contiguous() and t.data_ptr() % 16 == 0
+
+
+def greedy(logits: torch.Tensor) -> torch.Tensor:
+    """The lowest index of the largest logit of every row (int64)."""
+    if not (type(logits) is torch.Tensor and logits.is_cuda and logits.dim() == 2 and logits.is_contiguous() and
+            logits.dtype == torch.float32 and 0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
+        return torch.argmax(logits, dim=-1)
+    n, vocab = logits.shape
+    tokens = torch.empty(n, dtype=torch.int64, device=logits.device)
+    keys = torch.empty(n * ARGMAX_PARTS, dtype=torch.int64, device=logits.device)
+    S._check(_library().splice_decoder_argmax(logits.data_ptr(), n, vocab, tokens.data_ptr(), keys.data_ptr(),
+                                              S._stream_ptr(None, logits.device)), "splice_decoder_argmax")
+    return tokens
 
 
 def rms_norm(x: torch.Tensor, gain: torch.Tensor, eps: float) -> torch.Tensor:
@@ -78,9 +124,12 @@ class SweepDecoder:
         w, m, wt = self.w, self.m, self.wt
         C, Hq, Hkv, D = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim
         cdt = wt["embed"].dtype
+        x = wt["embed"][tokens]
+        if self._fused(x, pos):
+            return self._forward_fused(x, steps, pos)
+        x = x.float()
         if pos is None:
             pos = self.positions(steps)
-        x = wt["embed"][tokens].float()
         for l in range(self.N):
             p = wt["layers"][l]
             h = rms_norm(x, p["norm_1"], m.rms_eps).to(cdt)
@@ -98,11 +147,83 @@ class SweepDecoder:
                      @ p["w_down"]).float()
         return (rms_norm(x, wt["norm_f"], m.rms_eps).to(cdt) @ wt["lm_head"]).float()
 
+    def _fused(self, x: torch.Tensor, pos: Optional[torch.Tensor]) -> bool:
+        """Whether the library's kernels take this pass (x: the embedded tokens)."""
+        w, wt = self.w, self.wt
+        C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
+        if not (x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
+                (pos is None or (pos.is_cuda and tuple(pos.shape) == (C,)))):
+            return False
+        for p in wt["layers"]:
+            F = p["w_gate"].shape[-1]
+            if not (F % 8 == 0 and F > 0 and _plain(p["w_gate"], dev, d, F) and _plain(p["w_up"], dev, d, F) and
+                    _plain(p["w_down"], dev, F, d) and _plain(p["w_q"], dev, d, Hq * D) and
+                    _plain(p["w_k"], dev, d, Hkv * D) and _plain(p["w_v"], dev, d, Hkv * D) and
+                    _plain(p["w_o"], dev, Hq * D, d) and _plain(p["norm_1"], dev, d) and _dense(p["norm_1"]) and
+                    _plain(p["norm_2"], dev, d) and _dense(p["norm_2"])):
+                return False
+        head = wt["lm_head"]
+        return (_plain(wt["norm_f"], dev, d) and _dense(wt["norm_f"]) and head.dim() == 2 and
+                _plain(head, dev, d, head.shape[1]))
+
+    def _forward_fused(self, delta: torch.Tensor, steps, pos: Optional[torch.Tensor]) -> torch.Tensor:
+        """forward() with the library's kernels between the products: the same roundings, so the same bits up to the head."""
+        w, m, wt, lib = self.w, self.m, self.wt, _library()
+        C, Hq, Hkv, D, d, dev = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, delta.shape[1], delta.device
+        bf16, stream = torch.bfloat16, S._stream_ptr(None, delta.device)
+        ok = S._check
+        x = torch.empty((2, C, d), dtype=torch.float32, device=dev)   # the residual stream and its squares
+        x, sq = x[0], x[1]
+        h = torch.empty(((C + 15) // 16 * 16, d), dtype=bf16, device=dev)[:C]
+        o = torch.empty((C, Hq * D), dtype=bf16, device=dev)
+        tab = torch.empty((C, D), dtype=torch.float32, device=dev)
+        xp, sp, hp, op, tp, outp = (t.data_ptr() for t in (x, sq, h, o, tab, self.out))
+        st, stp = S._steps(steps, C)
+        if pos is not None:
+            pos = pos.to(torch.float64).contiguous()
+        ok(lib.splice_decoder_rope_table(tp, None if pos is None else pos.data_ptr(), stp, C, D, w.prompt_len,
+                                         float(m.rope_theta), stream), "splice_decoder_rope_table")
+
+        def norm(delta, gain, assign=0, packed=0):
+            """x += delta (the first: x = delta); h = bf16(rms_norm(x)), packed for the head."""
+            ok(lib.splice_decoder_residual(xp, delta.data_ptr(), sp, C * d, assign, stream), "splice_decoder_residual")
+            mean = sq.mean(-1, keepdim=True)
+            ok(lib.splice_decoder_norm(xp, mean.data_ptr(), gain.data_ptr(), hp, C, d, m.rms_eps, packed, stream),
+               "splice_decoder_norm")
+
+        first = 1
+        for l in range(self.N):
+            p, c = wt["layers"][l], self.caches[l]
+            norm(delta, p["norm_1"], first)
+            first = 0
+            q, k, v = h @ p["w_q"], h @ p["w_k"], h @ p["w_v"]
+            ok(lib.splice_decoder_rope(q.data_ptr(), k.data_ptr(), tp, C, Hq, Hkv, D, stream), "splice_decoder_rope")
+            S.splice_decode_step(self.shape, self.calls[l], self.lw, st, q, k, v, c["clean_k"], c["clean_v"],
+                                 c["donor_k"], c["donor_v"], c["gen_k"], c["gen_v"], self.out, self.lse, self.ws)
+            ok(lib.splice_decoder_round(outp, op, C * Hq * D, stream), "splice_decoder_round")
+            norm(o @ p["w_o"], p["norm_2"])
+            gate, up = h @ p["w_gate"], h @ p["w_up"]
+            ok(lib.splice_decoder_silu(gate.data_ptr(), up.data_ptr(), gate.data_ptr(), gate.numel(), stream),
+               "splice_decoder_silu")
+            delta = gate @ p["w_down"]
+        head = wt["lm_head"]
+        vocab = head.shape[1]
+        own_head = _dense(head) and d % 32 == 0 and vocab % 8 == 0 and 0 < vocab <= 1 << 24
+        norm(delta, wt["norm_f"], first, own_head)
+        if not own_head:
+            return (h @ head).float()
+        logits = torch.empty((C, vocab), dtype=torch.float32, device=dev)
+        need = ok(lib.splice_decoder_head_bytes(C, d, vocab), "splice_decoder_head_bytes")
+        part = torch.empty(need, dtype=torch.uint8, device=dev)
+        ok(lib.splice_decoder_head(hp, head.data_ptr(), logits.data_ptr(), C, d, vocab, part.data_ptr(), need, stream),
+           "splice_decoder_head")
+        return logits
+
     def step(self, tokens: torch.Tensor, steps: np.ndarray, pos: Optional[torch.Tensor] = None):
-        """One decode pass: (next tokens [C] int64, logits [C][V]).  argmax
-        returns the first maximal index, the lowest-index tie-break."""
+        """One decode pass: (next tokens [C] int64, logits [C][V]); of equal
+        largest logits the lowest index."""
         logits = self.forward(tokens, steps, pos)
-        return torch.argmax(logits, dim=-1), logits
+        return greedy(logits), logits
 
 
 def advance(steps: np.ndarray, next_tokens: np.ndarray, eos: int, n_steps: int) -> np.ndarray:

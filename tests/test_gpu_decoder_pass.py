@@ -1,0 +1,147 @@
+"""The fused decode pass (bf16 weights: this library's kernels between the
+products) against the same pass written out in PyTorch operations.
+
+The fused kernels round where the operations they replace round, so what
+enters and leaves every product is the same bit for bit: the appended cache
+rows are equal.  The head is the library's own product: the same bf16 inputs
+summed in fp32 in another order, then rounded to bf16 as the operation's
+output is, so a logit differs by at most one bf16 step (2^-7 of its size) plus
+both sums' own error, d 2^-24 times the sum of |h w| at most.  |h| is about 1
+and |w| about d^-1/2, so that sum is below 8 sqrt(d)."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_common as gc
+import paper_2605_30574_amd as sp
+import workloads
+from paper_2605_30574_amd import decode
+from workloads.model import ModelConfig, make_weights
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    sp.load_library()
+
+
+def _decoder(C, d, F, V, Hq, Hkv, D, N, seed=0):
+    w = workloads.get(1).with_(n_layers=N, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, prompt_len=40, span=(5, 33),
+                               n_steps=16, cells=tuple((i % (N + 1), i % 4) for i in range(C)), scale=D ** -0.5)
+    m = ModelConfig(d_model=d, d_ff=F, vocab=V, eos=0)
+    wt = make_weights(w, m, seed=seed, dtype=torch.bfloat16, device="cuda", draw_on_device=True)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    for L in wt["layers"]:
+        for n in ("norm_1", "norm_2"):
+            L[n] = (1 + 0.2 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    wt["norm_f"] = (1 + 0.2 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    lw = workloads.cell_lw(w)
+
+    def make(fused):
+        dec = decode.SweepDecoder(w, m, wt, [gc.gpu_layer(w, l) for l in range(N)], lw)
+        if not fused:
+            dec._fused = lambda *a: False
+        return dec
+    rng = np.random.default_rng(seed)
+    steps = rng.integers(0, w.n_steps, size=C).astype(np.int32)
+    tokens = torch.as_tensor(rng.integers(0, V, size=C), device="cuda")
+    return make, wt, tokens, steps
+
+
+def _compare(make, wt, tokens, steps, what, pos=None):
+    gc.announce(f"decoder pass {what}")
+    a, b = make(True), make(False)
+    assert a._fused(wt["embed"][tokens], pos), "the fused path did not take the pass"
+    tok, got = a.step(tokens, steps, pos)
+    want = b.forward(tokens, steps, pos)
+    torch.cuda.synchronize()
+    for ca, cb in zip(a.caches, b.caches):
+        for n in ("gen_k", "gen_v"):
+            assert torch.equal(ca[n].view(torch.int16), cb[n].view(torch.int16)), f"{what}: {n}"
+    d = wt["lm_head"].shape[0]
+    bound = 2.0 ** -7 * want.abs() + 2 * d * 2.0 ** -24 * 8 * d ** 0.5
+    assert torch.isfinite(got).all() and ((got - want).abs() <= bound).all(), what
+    assert torch.equal(tok, torch.argmax(got, -1)), what
+
+
+# rows around the head's row blocks, the smallest sizes, K and vocabulary with
+# partial column tiles, columns split over K in the last round (vocabulary 66600)
+@pytest.mark.parametrize("C,d,F,V,Hq,Hkv,D,N", [
+    (1, 32, 32, 8, 2, 1, 64, 1), (16, 96, 160, 136, 4, 2, 64, 2), (17, 256, 416, 1000, 8, 2, 64, 1),
+    (33, 320, 96, 264, 4, 4, 128, 2), (65, 128, 512, 520, 4, 2, 256, 1), (128, 512, 768, 4104, 8, 8, 64, 1),
+    (129, 224, 352, 264, 4, 2, 64, 1), (256, 256, 64, 512, 2, 1, 64, 1), (24, 1056, 64, 66600, 2, 1, 64, 1),
+    (100, 1056, 64, 66600, 2, 1, 64, 1), (9, 72, 104, 100, 4, 2, 64, 1)])
+def test_fused_pass_keeps_the_bits(C, d, F, V, Hq, Hkv, D, N):
+    make, wt, tokens, steps = _decoder(C, d, F, V, Hq, Hkv, D, N)
+    _compare(make, wt, tokens, steps, f"C={C} d={d} F={F} V={V} D={D}")
+
+
+def test_given_positions_finished_cells_and_strided_weights():
+    make, wt, tokens, steps = _decoder(20, 96, 160, 136, 4, 2, 64, 2)
+    for pos in (torch.arange(20, device="cuda") * 37, torch.arange(20, device="cuda").float() * 411.0):
+        _compare(make, wt, tokens, steps, f"positions {pos.dtype}", pos)
+    done = steps.copy()
+    done[3] = done[11] = -1   # their attention rows are not written: keep them finite in both
+    a, b = make(True), make(False)
+    a.out.zero_()
+    b.out.zero_()
+    got, want = a.forward(tokens, done), b.forward(tokens, done)
+    assert torch.allclose(got, want, rtol=2 ** -7, atol=1e-3)
+    for n in ("w_q", "w_down"):   # a transposed view is taken as it is
+        for L in wt["layers"]:
+            L[n] = L[n].t().contiguous().t()
+    wt["lm_head"] = wt["lm_head"].t().contiguous().t()
+    _compare(make, wt, tokens, steps, "strided weights")
+
+
+def test_other_weights_take_the_written_out_pass():
+    make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
+    dec = make(True)
+    x = wt["embed"][tokens]
+    assert dec._fused(x, None)
+    keep = wt["layers"][0]["norm_1"]
+    for bad in (keep.float(), torch.stack([keep, keep], 1)[:, 0]):   # another type, a strided gain
+        wt["layers"][0]["norm_1"] = bad
+        assert not dec._fused(x, None)
+        dec.forward(tokens, steps)
+    wt["layers"][0]["norm_1"] = keep.clone().requires_grad_()
+    assert not dec._fused(x, None)
+    with torch.no_grad():
+        assert dec._fused(x, None)
+    wt["layers"][0]["norm_1"] = keep
+    assert not dec._fused(x.float(), None) and not dec._fused(x, torch.arange(5))
+
+
+def test_norm_rounds_as_the_operations():
+    g = torch.Generator(device="cuda").manual_seed(3)
+    C, d, lib = 256, 1024, decode._library()
+    buf = torch.empty(2, C, d, device="cuda")
+    for scale in (1e-3, 1.0, 300.0):
+        x, delta = torch.randn(C, d, generator=g, device="cuda") * scale, torch.randn(C, d, generator=g, device="cuda").bfloat16()
+        gain = (1 + 0.2 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+        h = torch.empty(C, d, device="cuda", dtype=torch.bfloat16)
+        buf[0].copy_(x)
+        gc.announce(f"norm scale {scale}")
+        assert lib.splice_decoder_residual(buf[0].data_ptr(), delta.data_ptr(), buf[1].data_ptr(), C * d, 0, None) == 0
+        mean = buf[1].mean(-1, keepdim=True)
+        assert lib.splice_decoder_norm(buf[0].data_ptr(), mean.data_ptr(), gain.data_ptr(), h.data_ptr(), C, d, 1e-6, 0,
+                                       None) == 0
+        assert torch.equal(buf[0], x + delta.float())
+        assert torch.equal(h, decode.rms_norm(x + delta.float(), gain, 1e-6).bfloat16())
+
+
+@pytest.mark.parametrize("rows,vocab", [(1, 1), (3, 257), (130, 1023), (7, 70001)])
+def test_greedy_is_argmax(rows, vocab):
+    g = torch.Generator(device="cuda").manual_seed(rows)
+    x = torch.randint(-3, 4, (rows, vocab), generator=g, device="cuda").float()   # many ties
+    x[x == 0] = -0.0
+    gc.announce(f"greedy {rows}x{vocab}")
+    assert torch.equal(decode.greedy(x), torch.argmax(x, -1))
+    x[0, :] = float("-inf")
+    x[rows // 2, vocab // 2] = float("inf")
+    x[rows - 1, vocab - 1] = float("nan")
+    x[rows - 1, vocab // 3] = float("nan")
+    assert torch.equal(decode.greedy(x), torch.argmax(x, -1))
+    assert torch.equal(decode.greedy(x.double()), torch.argmax(x, -1))   # other types: the operation itself
