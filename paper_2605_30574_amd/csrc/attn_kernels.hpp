@@ -158,6 +158,7 @@ __device__ __forceinline__ void load_pslot(__amdgpu_buffer_rsrc_t r, uint32_t ba
 // of each head is wave-uniform (row groups combine with DPP, ds_swizzle and
 // readlane), so row groups never rescale against each other and the rescale
 // is a scalar branch; at the end their (l, o) are plain sums.
+constexpr int kRowsDeep = 4;   // rows a row group takes at once where few waves stream
 template <int D, int G, bool BF16>
 struct Valu {
     static constexpr int EB = BF16 ? 2 : 4;
@@ -169,7 +170,6 @@ struct Valu {
     static constexpr int RGR = 16 / LPK;                       // row groups per 16-lane DPP row
     static constexpr int ROW = D * EB;
     static constexpr int PSTRIDE = LPK * 16;
-    static constexpr int U = 4;
     static constexpr int QW = NP * 4;                          // q dwords per head per lane
     // element index of piece p, element e of lane lj
     static __device__ __forceinline__ int elem(int lj, int p, int e) { return p * LPK * EPP + lj * EPP + e; }
@@ -213,13 +213,13 @@ __device__ __forceinline__ void load_q(const AttnArgs &a, int c, int g, uint32_t
 }
 
 // row_of(key, &k_row, &v_row) -> false if the key is not to be attended
-// (its pointers must still be readable).  m is wave-uniform on return.
-template <int D, int G, bool BF16, class RowFn>
+// (its pointers must still be readable).  m is wave-uniform on return.  U: rows
+// a row group takes at once.
+template <int D, int G, bool BF16, int U, class RowFn>
 __device__ __forceinline__ void valu_stream(const uint32_t (&qr)[G][Valu<D, G, BF16>::QW], int kbeg, int kend,
                                             float qk_scale, RowFn row_of, float (&m)[G], float (&l)[G],
                                             float (&o)[G][Valu<D, G, BF16>::EL]) {
     using V = Valu<D, G, BF16>;
-    constexpr int U = V::U;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lj = lane % V::LPK, rg = lane / V::LPK;
     static_for<0, G>([&](auto h) {
@@ -394,7 +394,7 @@ __device__ void gen_item(const AttnArgs &a, int c, int g, int gk, char *buf) {
     const size_t off = ((size_t)c * a.Hkv + g) * (size_t)a.cap * V::ROW;
     const char *kb = a.gk + off, *vb = a.gv + off;
     float m[G], l[G], o[G][V::EL];
-    valu_stream<D, G, BF16>(qr, r0, r1, a.qk_scale,
+    valu_stream<D, G, BF16, kRowsDeep>(qr, r0, r1, a.qk_scale,
                             [&](int key, const char *&kp, const char *&vp) {
                                 kp = kb + (size_t)key * V::ROW;
                                 vp = vb + (size_t)key * V::ROW;
@@ -417,7 +417,7 @@ __device__ void prompt_item_valu(const AttnArgs &a, int c, int g, int pk, char *
     const bool spl = bit_set(a.spliced, c);
     const size_t head = (size_t)g * a.Tp * V::ROW;
     float m[G], l[G], o[G][V::EL];
-    valu_stream<D, G, BF16>(qr, k0, k1, a.qk_scale,
+    valu_stream<D, G, BF16, kRowsDeep>(qr, k0, k1, a.qk_scale,
                             [&](int j, const char *&kp, const char *&vp) {
                                 const bool in_span = j >= a.sa && j < a.sb;
                                 const bool donor = spl && in_span && !a.zero_donor;
@@ -1189,7 +1189,7 @@ void fused_kernel(AttnArgs a) {
 // writes out and lse itself.  No partial results and no merge; the prompt
 // tiles the cells share are re-read from L2.  Chosen by the host when the
 // prompt is short enough for that to be cheaper than the row-block path.
-template <int D, int G, bool BF16>
+template <int D, int G, bool BF16, int U>
 __global__ __launch_bounds__(kThreads) void cellwise_kernel(AttnArgs a) {
     using V = Valu<D, G, BF16>;
     __shared__ __attribute__((aligned(16))) char buf[kWaves * 4 * G * (D + 1) * 4 + kWaves * G * 4];
@@ -1206,7 +1206,7 @@ __global__ __launch_bounds__(kThreads) void cellwise_kernel(AttnArgs a) {
     const char *gkb = a.gk + ((size_t)c * a.Hkv + g) * (size_t)a.cap * V::ROW;
     const char *gvb = a.gv + ((size_t)c * a.Hkv + g) * (size_t)a.cap * V::ROW;
     float m[G], l[G], o[G][V::EL];
-    valu_stream<D, G, BF16>(qr, 0, n_list, a.qk_scale,
+    valu_stream<D, G, BF16, U>(qr, 0, n_list, a.qk_scale,
                             [&](int v, const char *&kp, const char *&vp) {
                                 if (v < n_pl) {
                                     int j = a.jp0 + v;
@@ -1238,20 +1238,30 @@ __global__ __launch_bounds__(kThreads) void cellwise_kernel(AttnArgs a) {
     });
 }
 
+}  // namespace splice_dev
+
+#include "wide_f32.hpp"
+
+namespace splice_dev {
+
 // ------------------------------------------------------------ dispatch
 
 typedef void (*attn_fn)(AttnArgs);
 struct AttnKernels {
     attn_fn items;      // one launch of prompt and generated-row items with merge
     attn_fn cellwise;   // f32, short prompts: one work group per (cell, KV head)
+    attn_fn cellwise_many;      // ... with fewer registers, for many work groups
+    attn_fn wide, wide_merge;   // f32, many rows over a prompt
 };
 
 template <int D, int G, bool BF16>
 AttnKernels kernels_of() {
     if constexpr (BF16)
-        return AttnKernels{fused_kernel<D, G>, nullptr};
+        return AttnKernels{fused_kernel<D, G>, nullptr, nullptr, nullptr, nullptr};
     else
-        return AttnKernels{items_kernel<D, G>, cellwise_kernel<D, G, BF16>};
+        return AttnKernels{items_kernel<D, G>, cellwise_kernel<D, G, BF16, G >= 8 && D <= 128 ? 1 : kRowsDeep>,
+                           cellwise_kernel<D, G, BF16, G >= 4 ? 1 : kRowsDeep>, wide_kernel<D, G>,
+                           wide_merge_kernel<D, G>};
 }
 
 template <int D, bool BF16>
@@ -1261,7 +1271,7 @@ AttnKernels pick_g(int G) {
     case 2: return kernels_of<D, 2, BF16>();
     case 4: return kernels_of<D, 4, BF16>();
     case 8: return kernels_of<D, 8, BF16>();
-    default: return AttnKernels{nullptr, nullptr};
+    default: return AttnKernels{};
     }
 }
 

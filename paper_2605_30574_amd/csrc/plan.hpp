@@ -233,8 +233,51 @@ inline void cut(int n, int target, int split, int *k, int *len, int min_chunk = 
 // which costs less than the split and merge of the item path.
 constexpr int kCellwiseMaxPrompt = 512;
 
+// Its work groups take four rows a row group at once, which hides the loads of
+// a list behind few waves, or one, which leaves registers for twice the waves
+// (at G = 4; at G = 8 four spill, at G <= 2 they fit): one where the call has
+// two work groups a compute unit or more (D = 128, G = 4: 512 work groups of
+// 133 keys 24.8 -> 18.7 us, of 613 keys 41.2 -> 34.9; 256 of 229 keys 14.8, with
+// one 15.8).
+constexpr int kCellwiseManyGroups = 512;
+
+inline bool cellwise_many(const splice_shape &sh) { return sh.n_cells * sh.n_kv_heads >= kCellwiseManyGroups; }
+
+// f32 calls whose cells share the reading of the prompt (wide_f32.hpp): the
+// other routes cost about what the rows' keys cost, this one a second launch
+// and the prompt items' start-up (10 to 14 us), so it takes calls with many
+// keys for each row group: G keys >= 1536 (D = 128, G = 4, 300 keys: 15.4 against
+// 15.7 us with 8 cells, 27.5 each with 64; 512 keys: 18.0 against 14.2, 34.9
+// against 31.2), at G = 8 (one work group a compute unit) above the cellwise
+// route's limit; and at least half a 64-row group (G = 4, 8 cells, 1024 keys:
+// 22.0 against 18.2).  At G <= 2 the vector ALUs do well until a compute unit
+// holds several (cell, KV head) pairs (D = 128, G = 1, 1500 keys, 128 pairs:
+// 17.3 against 19.7; D = 64, 256 pairs: 16.8 against 15.3).
+constexpr int kWideF32Rows = 32;
+constexpr int kWideF32Keys = 1536;
+constexpr int kWideF32Pairs = 256;
+constexpr int kWideF32Items = 256;               // prompt work groups aimed for: one a compute unit
+constexpr int kWideF32Chunk = 64;                // keys of a chunk, at least
+constexpr int kWideF32LongChunk = 256;           // ... and at most, up to kWideF32MaxChunks chunks
+constexpr int kWideF32MaxChunks = 16;
+constexpr int64_t kWideF32MaxBytes = (int64_t)64 << 20;   // partial results, at most
+
+inline int wide_f32_chunk_target(const splice_shape &sh) {
+    const int groups = sh.n_kv_heads * (ceil_div((int64_t)sh.n_cells * group_of(sh), group_rows(sh.head_dim)) + 1);
+    const int t = kWideF32Items / groups;
+    return t < 1 ? 1 : (t > kWideF32MaxChunks ? kWideF32MaxChunks : t);
+}
+
+inline bool wide_f32(const splice_shape &sh, int n_prompt, int n_p) {
+    const int G = group_of(sh);
+    return !bf16_path(sh) && sh.n_cells * G >= kWideF32Rows && (int64_t)n_prompt * G >= kWideF32Keys &&
+           (G < 8 || n_prompt > kCellwiseMaxPrompt) && (G > 2 || sh.n_cells * sh.n_kv_heads >= kWideF32Pairs) &&
+           (int64_t)sh.n_cells * sh.n_kv_heads * (n_p + 1) * slot_floats(G, sh.head_dim) * 4 <= kWideF32MaxBytes;
+}
+
 struct AttnPlan {
     bool cellwise;           // one work group per (cell, KV head), no partials
+    bool wide;               // f32: shared-prompt work groups and one per (cell, KV head)
     Geometry geo;
     int n_p, p_len;          // prompt chunks over the visible prompt
     int n_g, g_len;          // chunks over the visible generated rows
@@ -326,9 +369,30 @@ inline int count_clean(const splice_shape &sh, const splice_call &call, const in
 // different steps: the widest visible prompt and the longest generated part)
 // over n_active cells, n_clean of them unspliced.
 inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, const Geometry &geo, int n_clean,
-                              int n_active, const Residency &res = Residency(), bool same_rows = true) {
+                              int n_active, const Residency &res = Residency(), bool same_rows = true,
+                              bool wide_ok = true) {
     AttnPlan p;
     p.geo = geo;
+    p.wide = false;
+    if (wide_ok && !bf16_path(sh) && call.split_keys == 0 && geo.n_prompt > 0) {
+        p.n_p = wide_f32_chunk_target(sh);
+        const int least = ceil_div(geo.n_prompt, kWideF32LongChunk);   // short chains of sums
+        if (p.n_p < least) p.n_p = least < kWideF32MaxChunks ? least : kWideF32MaxChunks;
+        if (p.n_p > ceil_div(geo.n_prompt, kWideF32Chunk)) p.n_p = ceil_div(geo.n_prompt, kWideF32Chunk);
+        p.p_len = round_up(ceil_div(geo.n_prompt, p.n_p), 32);
+        p.n_p = ceil_div(geo.n_prompt, p.p_len);
+        if (wide_f32(sh, geo.n_prompt, p.n_p)) {
+            p.wide = true;
+            p.cellwise = false;
+            p.n_g = 1;
+            p.g_len = geo.n_gen;
+            p.n_slots = p.n_p + 1;
+            p.n_prompt_items = kXcds * row_groups(sh, n_clean, n_active) * ceil_div((int64_t)sh.n_kv_heads * p.n_p, kXcds);
+            p.n_gen_items = sh.n_cells * sh.n_kv_heads;
+            p.gen_pairs = 1;
+            return p;
+        }
+    }
     p.cellwise = !bf16_path(sh) && call.split_keys == 0 && p.geo.n_prompt <= kCellwiseMaxPrompt;
     if (p.cellwise) {
         p.n_p = p.n_g = 0;
@@ -465,7 +529,10 @@ inline int worst_default_slots(const splice_shape &sh) {
     // bf16: a decode step with one active cell takes the most chunks
     const int prompt = max_default_chunks(sh.prompt_len, prompt_chunk_target(sh, bf16_path(sh) ? 1 : sh.n_cells),
                                           bf16_path(sh) ? kWideMinChunk : kMinChunk);
-    return bf16_path(sh) ? prompt + 1 : prompt + max_default_chunks(sh.gen_capacity, gen_chunk_target(sh));
+    if (bf16_path(sh)) return prompt + 1;
+    const int items = prompt + max_default_chunks(sh.gen_capacity, gen_chunk_target(sh));
+    const int wide = max_default_chunks(sh.prompt_len, kWideF32MaxChunks, kWideF32Chunk) + 1;
+    return items > wide || !wide_f32(sh, sh.prompt_len, 1) ? items : wide;
 }
 
 }  // namespace splice

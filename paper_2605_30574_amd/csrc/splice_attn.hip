@@ -28,6 +28,8 @@
 //                   mask, per row, what that row's step does not see, and
 //                   finished cells get no rows and no work.
 //   items_kernel, cellwise_kernel   f32 inputs, vector ALUs.
+//   wide_kernel     f32 inputs, many rows over one prompt (wide_f32.hpp): the
+//                   prompt items on the fp32 matrix cores.
 //   fill_kernel     splice_workspace_init.
 //
 // ZERO donor: a ZERO slot has K = V = 0, so its score is exactly 0 and it
@@ -119,7 +121,7 @@ AttnKernels pick_attn(int D, int G, int dtype) {
     case 64: return bf16 ? attn_kernels_d64_bf16(G) : attn_kernels_d64_f32(G);
     case 128: return bf16 ? attn_kernels_d128_bf16(G) : attn_kernels_d128_f32(G);
     case 256: return bf16 ? attn_kernels_d256_bf16(G) : attn_kernels_d256_f32(G);
-    default: return AttnKernels{nullptr, nullptr};
+    default: return AttnKernels{};
     }
 }
 
@@ -166,7 +168,9 @@ splice::Residency residency(const void *kernel, int threads) {
 // a forked sweep plans over its diverged cells only, and by default fewer
 // computed cells take more prompt chunks (with an explicit split_keys the
 // chunks do not depend on them); without it, a call that computes every cell.
-int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call, bool every_count) {
+// An f32 call that takes the shared-prompt route when it has the space for its
+// slots can do with less (least).
+int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call, bool every_count, bool least = false) {
     int32_t rc = splice::validate_shape(shape);
     if (rc != SPLICE_OK) return rc;
     int n_slots;
@@ -178,8 +182,10 @@ int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call,
         const int n_lo = every_count && call->split_keys == 0 ? 1 : n_hi;
         n_slots = 0;
         for (int n = n_lo; n <= n_hi; ++n) {   // the slots do not depend on the cell split
-            const int k = splice::plan_from_geo(*shape, *call, geo, 0, n).n_slots;
+            const int k = splice::plan_from_geo(*shape, *call, geo, 0, n, splice::Residency(), true, false).n_slots;
+            const int wide = least ? 0 : splice::plan_from_geo(*shape, *call, geo, 0, n).n_slots;
             n_slots = k > n_slots ? k : n_slots;
+            n_slots = wide > n_slots ? wide : n_slots;
         }
         if (n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
     } else {
@@ -379,10 +385,11 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
     if (!kern.items) return SPLICE_EUNSUPPORTED;
     const int threads = splice::bf16_path(sh) ? 64 * splice::fused_waves(sh.head_dim) : kThreads;
 
-    const splice::AttnPlan plan = splice::plan_from_geo(
-        sh, hi_call, geo, n_clean, n_active,
-        splice::bf16_path(sh) ? residency((const void *)kern.items, threads) : splice::Residency(),
-        g_lo.n_gen == g_hi.n_gen);
+    const splice::Residency res =
+        splice::bf16_path(sh) ? residency((const void *)kern.items, threads) : splice::Residency();
+    splice::AttnPlan plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, g_lo.n_gen == g_hi.n_gen);
+    if (plan.wide && workspace_bytes < splice::workspace_layout(sh, plan.n_slots).total)   // the route with fewer slots
+        plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, true, false);
     if (plan.n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
     const splice::WorkspaceLayout wl = splice::workspace_layout(sh, plan.n_slots);
     if (!workspace || !splice::aligned(workspace, 256)) return SPLICE_EWORKSPACE;
@@ -457,19 +464,25 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
         for (int i = n_gc; i < SPLICE_MAX_CELLS; ++i) a.gorder[i] = 0;
     }
     for (; n < SPLICE_MAX_CELLS; ++n) a.order[n] = 0;
-    if (splice::bf16_path(sh)) {
+    if (splice::bf16_path(sh) || plan.wide) {
         a.n_rb = splice::row_groups(sh, a.n_clean, a.n_active);
         a.n_rg_clean = splice::clean_row_groups(sh, a.n_clean);
     }
 
     if (plan.cellwise) {
-        hipLaunchKernelGGL(kern.cellwise, dim3((unsigned)(sh.n_cells * sh.n_kv_heads)), dim3(kThreads), 0,
-                           (hipStream_t)stream, a);
+        hipLaunchKernelGGL(splice::cellwise_many(sh) ? kern.cellwise_many : kern.cellwise,
+                           dim3((unsigned)(sh.n_cells * sh.n_kv_heads)), dim3(kThreads), 0, (hipStream_t)stream, a);
         return launch_status();
     }
     const int64_t items = (int64_t)plan.n_prompt_items + plan.n_gen_items;
     if (items > INT32_MAX) return SPLICE_EUNSUPPORTED;
-    hipLaunchKernelGGL(kern.items, dim3((unsigned)items), dim3((unsigned)threads), 0, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(plan.wide ? kern.wide : kern.items, dim3((unsigned)items), dim3((unsigned)threads), 0,
+                       (hipStream_t)stream, a);
+    if (plan.wide) {
+        const int64_t units = (int64_t)sh.n_cells * sh.n_q_heads * (sh.head_dim / 4);
+        hipLaunchKernelGGL(kern.wide_merge, dim3((unsigned)((units + kThreads - 1) / kThreads)), dim3(kThreads), 0,
+                           (hipStream_t)stream, a);
+    }
     return launch_status();
 }
 
@@ -529,7 +542,7 @@ int32_t splice_decode_attn_noalloc(const splice_shape *shape, const splice_call 
                                    void *stream) {
     // validation and the size check come first: a call that does not fit is
     // rejected before any device work
-    const int64_t need = attn_workspace_bytes(shape, call, false);   // every cell is computed
+    const int64_t need = attn_workspace_bytes(shape, call, false, true);   // every cell is computed
     if (need < 0) return (int32_t)need;
     if (need > (int64_t)SPLICE_NOALLOC_WORKSPACE_BYTES) return SPLICE_EWORKSPACE;
     void *ws = nullptr;

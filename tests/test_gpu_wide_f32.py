@@ -1,0 +1,110 @@
+"""float32 calls over a shared prompt on the fp32 matrix cores, against the
+fp64 oracle and against the general route.
+
+The products and sums are fp32, as on the general route; an output is a convex
+combination of values of size v with at most n terms, so the two differ by a
+few n 2^-24 v in the worst case and by a few 2^-24 sqrt(n) v as seen; 2e-5 of
+the largest value bounds both at these sizes (n <= 1400, |v| <= 6)."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_common as gc
+import paper_2605_30574_amd as sp
+import workloads
+from workloads import DONOR_BLANK, DONOR_DIFF, DONOR_ZERO
+
+pytestmark = pytest.mark.gpu
+ABS = 1.2e-4
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    sp.load_library()
+
+
+def _w(C, Hq, Hkv, D, Tp, span, donor, window=0, steps=20):
+    N = 4
+    cells = tuple((i % (N + 1), (0, 2, 9)[i % 3]) for i in range(C))
+    return workloads.get("qwen3-4b").with_(n_layers=N, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, prompt_len=Tp, span=span,
+                                           n_steps=steps, cells=cells, donor=donor, dtype="f32", scale=D ** -0.5,
+                                           local_window=window)
+
+
+# rows that fill and do not fill a 64-row group, prompts that end inside a tile
+# and a chunk, spans on and off tile edges, every donor, a window, every head size
+CASES = {
+    "d128-g4": (8, 32, 8, 128, 512, (40, 480), DONOR_BLANK),
+    "d128-g4-ragged": (17, 8, 2, 128, 1031, (33, 999), DONOR_DIFF),
+    "d128-g4-zero": (9, 8, 2, 128, 777, (16, 776), DONOR_ZERO),
+    "d128-g4-window": (16, 8, 2, 128, 900, (100, 800), DONOR_BLANK, 500),
+    "d64-g8": (5, 16, 2, 64, 530, (3, 529), DONOR_BLANK),
+    "d64-g8-zero-full": (33, 8, 1, 64, 1300, (0, 1300), DONOR_ZERO),
+    "d256-g2": (33, 16, 8, 256, 769, (64, 700), DONOR_DIFF),
+    "d256-g4": (8, 4, 1, 256, 400, (7, 391), DONOR_BLANK),
+    "d64-g1": (64, 4, 4, 64, 1537, (1, 1536), DONOR_BLANK),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_shared_prompt_route(name):
+    w = _w(*CASES[name])
+    lw = workloads.cell_lw(w)
+    shape = gc.shape_of(w)
+    for layer, step in ((0, 0), (2, 5), (3, 19)):
+        bufs = gc.gpu_layer(w, layer)
+        hb = gc.host(bufs)
+        q = workloads.make_q(w, layer, step, device="cuda")
+        call = sp.make_call(layer, step, w.window(layer), w.scale)
+        gc.announce(f"wide f32 {name} layer={layer} step={step}")
+        out, lse = gc.run_attn(w, layer, step, bufs, q, lw)
+        ref_o, ref_l = gc.run_oracle(w, layer, step, hb, workloads.to_numpy(q), lw)
+        assert np.abs(out - ref_o).max() <= ABS and np.abs(lse - ref_l).max() <= 1e-5 * max(1.0, np.abs(ref_l).max())
+        o2, l2 = gc.run_attn(w, layer, step, bufs, q, lw)
+        assert np.array_equal(out, o2) and np.array_equal(lse, l2), "repeat call"
+        # a workspace without the route's slots, and a given split: the general route
+        need = sp.splice_decode_attn_workspace_bytes(shape, call)
+        small = torch.empty(need, dtype=torch.uint8, device="cuda")[: need // 256 * 256]
+        sp.splice_workspace_init(small)
+        for nbytes in (need, need - 256):
+            o3 = torch.full((w.n_cells, w.n_q_heads, w.head_dim), float("nan"), device="cuda")
+            l3 = torch.full((w.n_cells, w.n_q_heads), float("nan"), device="cuda")
+            try:
+                sp.splice_decode_attn(shape, call, lw, q, bufs["clean_k"], bufs["clean_v"], bufs["donor_k"],
+                                      bufs["donor_v"], bufs["gen_k"], bufs["gen_v"], o3, l3, small[:nbytes])
+            except sp.SpliceError as e:   # the general route needs as much
+                assert e.status == sp.SPLICE_EWORKSPACE and nbytes < need
+                continue
+            assert np.abs(o3.cpu().numpy() - ref_o).max() <= ABS
+        o4, _ = gc.run_attn(w, layer, step, bufs, q, lw, split=256)
+        assert np.abs(o4 - ref_o).max() <= ABS
+
+
+def test_donor_equal_clean_is_unspliced_up_to_grouping():
+    """Spliced and unspliced cells sit in different row groups, which share no
+    arithmetic: the bits of a cell depend on neither."""
+    w = _w(16, 8, 2, 128, 700, (40, 650), DONOR_BLANK)
+    lw = workloads.cell_lw(w)
+    never = np.array([[w.n_layers, 0]] * w.n_cells, dtype=np.int32)
+    bufs = gc.gpu_layer(w, 2)
+    same = dict(bufs, donor_k=bufs["clean_k"], donor_v=bufs["clean_v"])
+    q = workloads.make_q(w, 2, 5, device="cuda")
+    gc.announce("wide f32 donor == clean")
+    o_u, l_u = gc.run_attn(w, 2, 5, bufs, q, never)
+    o_s, l_s = gc.run_attn(w, 2, 5, same, q, lw)
+    # a spliced cell's list is cut at the span's edges, an unspliced cell's too
+    assert np.array_equal(o_u, o_s) and np.array_equal(l_u, l_s)
+
+
+def test_many_short_lists():
+    """Cellwise calls with two work groups a compute unit and fewer."""
+    for C, Hkv, G in ((128, 4, 4), (64, 8, 4), (40, 2, 4), (6, 1, 8)):
+        w = _w(C, Hkv * G, Hkv, 64, 37, (3, 30), DONOR_BLANK)
+        lw = workloads.cell_lw(w)
+        bufs = gc.gpu_layer(w, 1)
+        q = workloads.make_q(w, 1, 19, device="cuda")
+        gc.announce(f"cellwise C={C} Hkv={Hkv} G={G}")
+        out, lse = gc.run_attn(w, 1, 19, bufs, q, lw)
+        ref_o, ref_l = gc.run_oracle(w, 1, 19, gc.host(bufs), workloads.to_numpy(q), lw)
+        assert np.abs(out - ref_o).max() <= ABS and np.abs(lse - ref_l).max() <= 1e-5 * max(1.0, np.abs(ref_l).max())
