@@ -1240,6 +1240,7 @@ __global__ __launch_bounds__(kThreads) void cellwise_kernel(AttnArgs a) {
 
 }  // namespace splice_dev
 
+#include "direct.hpp"
 #include "wide_f32.hpp"
 
 namespace splice_dev {
@@ -1252,16 +1253,19 @@ struct AttnKernels {
     attn_fn cellwise;   // f32, short prompts: one work group per (cell, KV head)
     attn_fn cellwise_many;      // ... with fewer registers, for many work groups
     attn_fn wide, wide_merge;   // f32, many rows over a prompt
+    attn_fn direct;     // bf16, short lists: one work group per (cell, KV head)
+    int direct_threads;
 };
 
 template <int D, int G, bool BF16>
 AttnKernels kernels_of() {
     if constexpr (BF16)
-        return AttnKernels{fused_kernel<D, G>, nullptr, nullptr, nullptr, nullptr};
+        return AttnKernels{fused_kernel<D, G>, nullptr, nullptr, nullptr, nullptr, direct_kernel<D, G>,
+                           DirectWaves<D>::NT};
     else
         return AttnKernels{items_kernel<D, G>, cellwise_kernel<D, G, BF16, G >= 8 && D <= 128 ? 1 : kRowsDeep>,
                            cellwise_kernel<D, G, BF16, G >= 4 ? 1 : kRowsDeep>, wide_kernel<D, G>,
-                           wide_merge_kernel<D, G>};
+                           wide_merge_kernel<D, G>, nullptr, 0};
 }
 
 template <int D, bool BF16>

@@ -468,6 +468,24 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
     return p;
 }
 
+// bf16 calls at one step whose (cell, KV head) pairs stream their own lists
+// (direct.hpp): while a list is short enough for one work group and the pairs'
+// repeated reads of the prompt do not add up.  The limits, in keys a list, for
+// one, two and three work groups a compute unit, from both kernels' times (us,
+// shared-prompt kernel against direct, 8 KV heads, G = 4 unless named): D = 128
+// 379 keys 14.5 / 12.2, 518 keys 11.9 / 13.5; 320 pairs of 134 keys 11.9 / 10.4,
+// of 189 12.8 / 12.6; 640 pairs of 38 keys 11.1 / 9.6, of 93 11.8 / 11.8.
+// D = 64 321 keys 12.3 / 10.2, 711 keys 9.8 / 12.4; 400 pairs of 211 keys
+// 11.4 / 10.2, of 321 12.5 / 12.3.  D = 256 211 keys 12.8 / 12.1, 321 keys
+// 13.9 / 15.3; 320 pairs of 51 keys 13.0 / 10.6, of 161 16.5 / 19.1.
+inline bool direct_bf16(const splice_shape &sh, int n_vis, int n_active, int n_cu) {
+    if (!bf16_path(sh) || n_active <= 0 || n_cu <= 0) return false;
+    const int per_cu = ceil_div((int64_t)n_active * sh.n_kv_heads, n_cu);
+    if (per_cu > 3) return false;
+    const int limit[3][3] = {{384, 256, 64}, {384, 160, 64}, {224, 96, 0}};   // D = 64, 128, 256
+    return n_vis <= limit[sh.head_dim <= 64 ? 0 : (sh.head_dim <= 128 ? 1 : 2)][per_cu - 1];
+}
+
 // bf16: the generated-row items load V non-temporally, so that the rows,
 // read once, do not push the shared prompt tiles out of the caches, when
 // the prompt caches a call reads (clean, plus donor when the donor is a

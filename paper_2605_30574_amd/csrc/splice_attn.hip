@@ -27,6 +27,8 @@
 //                   items cover the widest visible prompt of the call and
 //                   mask, per row, what that row's step does not see, and
 //                   finished cells get no rows and no work.
+//   direct_kernel   bf16 inputs, short lists (direct.hpp): one work group per
+//                   (cell, KV head), no partial results.
 //   items_kernel, cellwise_kernel   f32 inputs, vector ALUs.
 //   wide_kernel     f32 inputs, many rows over one prompt (wide_f32.hpp): the
 //                   prompt items on the fp32 matrix cores.
@@ -472,6 +474,13 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
     if (plan.cellwise) {
         hipLaunchKernelGGL(splice::cellwise_many(sh) ? kern.cellwise_many : kern.cellwise,
                            dim3((unsigned)(sh.n_cells * sh.n_kv_heads)), dim3(kThreads), 0, (hipStream_t)stream, a);
+        return launch_status();
+    }
+    if (!ragged && call->split_keys == 0 && call->merge_wait >= 0 &&
+        splice::direct_bf16(sh, geo.n_vis, n_active, res.n_cu)) {
+        // no partial results: the workspace, checked above all the same, is not used
+        hipLaunchKernelGGL(kern.direct, dim3((unsigned)(a.n_gen_cells * sh.n_kv_heads)),
+                           dim3((unsigned)kern.direct_threads), 0, (hipStream_t)stream, a);
         return launch_status();
     }
     const int64_t items = (int64_t)plan.n_prompt_items + plan.n_gen_items;

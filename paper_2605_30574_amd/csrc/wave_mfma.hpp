@@ -33,25 +33,28 @@ enum SegCols : int {
     kColsDonor = 2,   // columns of spliced cells (span read from the donor cache)
 };
 
-// An ordered key list made of up to kMaxSeg segments; the rows of a segment
+// An ordered key list made of up to NSEG segments; the rows of a segment
 // are contiguous (row stride D bf16) from k[s] / v[s].  Tiles never straddle
 // a segment, so tile boundaries depend only on the segment lengths.
-struct KeyList {
-    const char *k[kMaxSeg];
-    const char *v[kMaxSeg];
-    int len[kMaxSeg];
-    int cols[kMaxSeg];             // SegCols
-    int key0[kMaxSeg];             // position of the segment's first key (prompt slots)
-    int first_tile[kMaxSeg + 1];   // tiles before segment s; [n_seg] = total
+template <int NSEG>
+struct KeyListN {
+    const char *k[NSEG];
+    const char *v[NSEG];
+    int len[NSEG];
+    int cols[NSEG];             // SegCols
+    int key0[NSEG];             // position of the segment's first key (prompt slots)
+    int first_tile[NSEG + 1];   // tiles before segment s; [n_seg] = total
     int n_seg;
 };
+using KeyList = KeyListN<kMaxSeg>;
 
-__device__ __forceinline__ void list_init(KeyList &L) {
+template <int NSEG>
+__device__ __forceinline__ void list_init(KeyListN<NSEG> &L) {
     L.n_seg = 0;
 #pragma unroll
-    for (int s = 0; s <= kMaxSeg; ++s) L.first_tile[s] = 0;
+    for (int s = 0; s <= NSEG; ++s) L.first_tile[s] = 0;
 #pragma unroll
-    for (int s = 0; s < kMaxSeg; ++s) {
+    for (int s = 0; s < NSEG; ++s) {
         L.k[s] = nullptr;
         L.v[s] = nullptr;
         L.len[s] = 0;
@@ -64,13 +67,13 @@ __device__ __forceinline__ void list_init(KeyList &L) {
 // TK keys (a list is built and walked with one TK).  The segment index only
 // takes constant values after unrolling, so the list stays in scalar
 // registers.
-template <int TK = kTileKeys>
-__device__ __forceinline__ void list_add(KeyList &L, const char *k, const char *v, int n, int cols = kColsAll,
+template <int TK = kTileKeys, int NSEG = kMaxSeg>
+__device__ __forceinline__ void list_add(KeyListN<NSEG> &L, const char *k, const char *v, int n, int cols = kColsAll,
                                          int key0 = 0) {
     if (n <= 0) return;
     const int tiles = (n + TK - 1) / TK;
 #pragma unroll
-    for (int s = 0; s < kMaxSeg; ++s) {
+    for (int s = 0; s < NSEG; ++s) {
         if (s == L.n_seg) {
             L.k[s] = k;
             L.v[s] = v;
@@ -85,10 +88,11 @@ __device__ __forceinline__ void list_add(KeyList &L, const char *k, const char *
     L.n_seg += 1;
 }
 
-__device__ __forceinline__ int list_tiles(const KeyList &L) {
+template <int NSEG>
+__device__ __forceinline__ int list_tiles(const KeyListN<NSEG> &L) {
     int t = 0;
 #pragma unroll
-    for (int s = 0; s < kMaxSeg; ++s)
+    for (int s = 0; s < NSEG; ++s)
         if (s < L.n_seg) t = L.first_tile[s + 1];
     return t;
 }
@@ -102,12 +106,12 @@ struct TileRef {
     int key0;
 };
 
-template <int TK = kTileKeys>
-__device__ __forceinline__ TileRef list_tile(const KeyList &L, int t, int row_bytes) {
+template <int TK = kTileKeys, int NSEG = kMaxSeg>
+__device__ __forceinline__ TileRef list_tile(const KeyListN<NSEG> &L, int t, int row_bytes) {
     TileRef r{L.k[0], L.v[0], 0, kColsAll, 0};
     int off = t;
 #pragma unroll
-    for (int s = 0; s < kMaxSeg; ++s) {
+    for (int s = 0; s < NSEG; ++s) {
         if (s < L.n_seg && t >= L.first_tile[s]) {
             off = t - L.first_tile[s];
             r.k = L.k[s];
@@ -129,10 +133,11 @@ __device__ __forceinline__ TileRef list_tile(const KeyList &L, int t, int row_by
 // row load returns 0 without a memory access.  Issuing loads for it keeps the
 // number of loads in flight the same on every path, which lets the compiler
 // wait for exactly the tile it needs instead of for all of them.
-__device__ __forceinline__ TileRef empty_tile(const KeyList &L) { return TileRef{L.k[0], L.v[0], 0, kColsAll, 0}; }
+template <int NSEG>
+__device__ __forceinline__ TileRef empty_tile(const KeyListN<NSEG> &L) { return TileRef{L.k[0], L.v[0], 0, kColsAll, 0}; }
 
-template <int TK = kTileKeys>
-__device__ __forceinline__ TileRef list_tile_or_empty(const KeyList &L, int t, int n_tiles, int row_bytes) {
+template <int TK = kTileKeys, int NSEG = kMaxSeg>
+__device__ __forceinline__ TileRef list_tile_or_empty(const KeyListN<NSEG> &L, int t, int n_tiles, int row_bytes) {
     return t < n_tiles ? list_tile<TK>(L, t, row_bytes) : empty_tile(L);
 }
 
@@ -302,8 +307,8 @@ __device__ __forceinline__ void tile_compute(const u32x4_t (&kr)[WaveMfma<D>::ND
 // the cache policies of the K and the V row loads (0 normal, 2
 // non-temporal); they are constants so that every path issues the same
 // loads.
-template <int D, int DEPTH, int KAUX, int VAUX>
-__device__ __forceinline__ void wave_stream(const KeyList &L, int first, int step, const ColMask &cm,
+template <int D, int DEPTH, int KAUX, int VAUX, int NSEG = kMaxSeg>
+__device__ __forceinline__ void wave_stream(const KeyListN<NSEG> &L, int first, int step, const ColMask &cm,
                                             const bf16x8_t (&qb)[WaveMfma<D>::NDS], float qk_scale, char *sVt,
                                             WaveState<D> &S) {
     const int n_tiles = list_tiles(L);
