@@ -51,20 +51,23 @@ class SpliceError(RuntimeError):
 
 
 _lib = None
+_torch = None                # torch, once the library is loaded
+_current_raw_stream = None   # device index -> handle of its current stream, without a Stream object
 
 
 def load_library(path: str = LIB_PATH):
     """Load libsplice_attn.so (after torch, so both share one HIP runtime)."""
-    global _lib
+    global _lib, _torch, _current_raw_stream
     if _lib is not None:
         return _lib
-    import torch  # noqa: F401  -- maps torch's libamdhip64 before ours resolves it
+    import torch  # maps torch's libamdhip64 before ours resolves it
+    _torch, _current_raw_stream = torch, getattr(torch._C, "_cuda_getCurrentRawStream", None)
     if not os.path.exists(path):
         raise ImportError(f"{path} is not built; run `python -m paper_2605_30574_amd.build`")
     lib = ctypes.CDLL(path)
     vp, i32 = ctypes.c_void_p, ctypes.c_int32
     shp, cal = ctypes.POINTER(SpliceShape), ctypes.POINTER(SpliceCall)
-    i32p = ctypes.POINTER(ctypes.c_int32)
+    i32p = vp   # host int32 arrays, by address
     lib.splice_abi_version.restype = i32
     lib.splice_abi_version.argtypes = []
     lib.splice_status_str.restype = ctypes.c_char_p
@@ -126,20 +129,25 @@ def make_call(layer: int, step: int, window: int, scale: float, split_keys: int 
     return SpliceCall(layer, step, window, float(scale), split_keys, merge_wait)
 
 
+def _host_i32(x, rows: int, cols: int, name: str, what: str):
+    """(array, address) of a contiguous host int32 array of rows x cols values; keep the array for the call."""
+    if not (type(x) is np.ndarray and x.dtype == np.int32 and x.size == rows * cols and x.flags.c_contiguous):
+        x = np.ascontiguousarray(np.asarray(x, dtype=np.int32).reshape((-1, cols) if cols > 1 else -1))
+        if x.shape[0] != rows:
+            raise ValueError(f"{name} has {x.shape[0]} {what}, shape says {rows} cells")
+    return x, x.__array_interface__["data"][0]
+
+
 def _cells(cell_LW, n_cells: int):
-    a = np.ascontiguousarray(np.asarray(cell_LW, dtype=np.int32).reshape(-1, 2))
-    if a.shape[0] != n_cells:
-        raise ValueError(f"cell_LW has {a.shape[0]} rows, shape says {n_cells} cells")
-    return a, a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+    return _host_i32(cell_LW, n_cells, 2, "cell_LW", "rows")
 
 
 def _torch_dtype(shape: SpliceShape):
-    import torch
-    return torch.bfloat16 if shape.dtype == SPLICE_BF16 else torch.float32
+    return _torch.bfloat16 if shape.dtype == SPLICE_BF16 else _torch.float32
 
 
 def _dev_ptr(t, name: str, numel: int, dtype, device=None, optional: bool = False):
-    """Pointer of a contiguous GPU tensor of exactly ``numel`` elements."""
+    """Address of a contiguous GPU tensor of exactly ``numel`` elements, and its device."""
     if t is None:
         if optional:
             return None, device
@@ -156,26 +164,51 @@ def _dev_ptr(t, name: str, numel: int, dtype, device=None, optional: bool = Fals
         raise ValueError(f"{name} has {t.numel()} elements, expected {numel}")
     if device is not None and t.device != device:
         raise ValueError(f"{name} is on {t.device}, expected {device}")
-    return ctypes.c_void_p(t.data_ptr()), t.device
+    return t.data_ptr(), t.device
+
+
+def _ptr(t, name: str, numel: int, dtype, dev):
+    """_dev_ptr of a tensor on ``dev`` = (device index, device): the checks of the usual case in as few calls as they take
+    (a call of the binding makes up to a dozen of them)."""
+    if numel > 0 and t is not None and t.dtype is dtype and t.is_cuda and t.get_device() == dev[0] and \
+            t.numel() == numel and t.is_contiguous():
+        return t.data_ptr()
+    return _dev_ptr(t, name, numel, dtype, dev[1])[0]
 
 
 def _stream_ptr(stream, device):
-    import torch
     if stream is None:
-        stream = torch.cuda.current_stream(device)
+        return _raw_stream(device)
     if isinstance(stream, int):
-        return ctypes.c_void_p(stream)
-    return ctypes.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
-def _donors(shape: SpliceShape, donor_k, donor_v, dt, n_prompt, dev):
+def _raw_stream(device):
+    """Handle of the current stream of ``device`` (a device, or its index)."""
+    index = device if isinstance(device, int) else device.index
+    if _current_raw_stream is not None and index is not None:
+        return _current_raw_stream(index)
+    return _torch.cuda.current_stream(device).cuda_stream
+
+
+def _attn_ptrs(shape: SpliceShape, q, clean_k, clean_v, donor_k, donor_v, gen_k, gen_v, out, lse):
+    """((device index, device), addresses) of the tensors every attention call takes, checked against the shape."""
+    C, Hq, Hkv, D = shape.n_cells, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
+    dt = _torch_dtype(shape)
+    n_prompt, n_gen, n_out = Hkv * shape.prompt_len * D, C * Hkv * shape.gen_capacity * D, C * Hq * D
+    qp, device = _dev_ptr(q, "q", n_out, dt)
+    dev = (q.get_device(), device)
+    ck, cv = _ptr(clean_k, "clean_k", n_prompt, dt, dev), _ptr(clean_v, "clean_v", n_prompt, dt, dev)
     if shape.donor_kind == SPLICE_DONOR_ZERO:
         if donor_k is not None or donor_v is not None:
             raise ValueError("the ZERO donor takes no donor buffers")
-        return None, None
-    dk, _ = _dev_ptr(donor_k, "donor_k", n_prompt, dt, dev)
-    dv, _ = _dev_ptr(donor_v, "donor_v", n_prompt, dt, dev)
-    return dk, dv
+        dk = dv = None
+    else:
+        dk, dv = _ptr(donor_k, "donor_k", n_prompt, dt, dev), _ptr(donor_v, "donor_v", n_prompt, dt, dev)
+    f32 = _torch.float32
+    return dev, (qp, ck, cv, dk, dv, _ptr(gen_k, "gen_k", n_gen, dt, dev), _ptr(gen_v, "gen_v", n_gen, dt, dev),
+                 _ptr(out, "out", n_out, f32, dev), _ptr(lse, "lse", C * Hq, f32, dev))
 
 
 # ------------------------------------------------------------------ C entry points
@@ -201,17 +234,18 @@ def splice_decode_attn_workspace_bytes(shape: SpliceShape, call: Optional[Splice
 
 
 def splice_workspace_init(workspace, stream=None) -> None:
+    lib = load_library()
     p, dev = _dev_ptr(workspace, "workspace", None, None)
     nbytes = workspace.numel() * workspace.element_size()
-    _check(load_library().splice_workspace_init(p, nbytes, _stream_ptr(stream, dev)), "splice_workspace_init")
+    _check(lib.splice_workspace_init(p, nbytes, _stream_ptr(stream, dev)), "splice_workspace_init")
 
 
 def splice_workspace_handovers(workspace, stream=None) -> int:
     """Merges handed over since the workspace was initialised (synchronises ``stream``)."""
+    lib = load_library()
     p, dev = _dev_ptr(workspace, "workspace", None, None)
     nbytes = workspace.numel() * workspace.element_size()
-    return _check(load_library().splice_workspace_handovers(p, nbytes, _stream_ptr(stream, dev)),
-                  "splice_workspace_handovers")
+    return _check(lib.splice_workspace_handovers(p, nbytes, _stream_ptr(stream, dev)), "splice_workspace_handovers")
 
 
 def new_workspace(shape: SpliceShape, call: Optional[SpliceCall] = None, device="cuda", stream=None):
@@ -225,7 +259,6 @@ def new_workspace(shape: SpliceShape, call: Optional[SpliceCall] = None, device=
 
 def splice_kv_build(shape: SpliceShape, call: SpliceCall, cell_LW, clean_k, clean_v, donor_k, donor_v,
                     gen_k, gen_v, out_k, out_v, out_src, stream=None) -> None:
-    import torch
     lib = load_library()
     C, Hkv, D = shape.n_cells, shape.n_kv_heads, shape.head_dim
     n_vis = splice_visible_len(shape, call)
@@ -233,12 +266,18 @@ def splice_kv_build(shape: SpliceShape, call: SpliceCall, cell_LW, clean_k, clea
     n_prompt = Hkv * shape.prompt_len * D
     ck, dev = _dev_ptr(clean_k, "clean_k", n_prompt, dt)
     cv, _ = _dev_ptr(clean_v, "clean_v", n_prompt, dt, dev)
-    dk, dv = _donors(shape, donor_k, donor_v, dt, n_prompt, dev)
+    if shape.donor_kind == SPLICE_DONOR_ZERO:
+        if donor_k is not None or donor_v is not None:
+            raise ValueError("the ZERO donor takes no donor buffers")
+        dk = dv = None
+    else:
+        dk, _ = _dev_ptr(donor_k, "donor_k", n_prompt, dt, dev)
+        dv, _ = _dev_ptr(donor_v, "donor_v", n_prompt, dt, dev)
     gk, _ = _dev_ptr(gen_k, "gen_k", C * Hkv * shape.gen_capacity * D, dt, dev)
     gv, _ = _dev_ptr(gen_v, "gen_v", C * Hkv * shape.gen_capacity * D, dt, dev)
     ok, _ = _dev_ptr(out_k, "out_k", C * Hkv * n_vis * D, dt, dev)
     ov, _ = _dev_ptr(out_v, "out_v", C * Hkv * n_vis * D, dt, dev)
-    os_, _ = _dev_ptr(out_src, "out_src", C * n_vis, torch.uint8, dev)
+    os_, _ = _dev_ptr(out_src, "out_src", C * n_vis, _torch.uint8, dev)
     lw, lwp = _cells(cell_LW, C)
     _check(lib.splice_kv_build(ctypes.byref(shape), ctypes.byref(call), lwp, ck, cv, dk, dv, gk, gv,
                                ok, ov, os_, _stream_ptr(stream, dev)), "splice_kv_build")
@@ -246,53 +285,28 @@ def splice_kv_build(shape: SpliceShape, call: SpliceCall, cell_LW, clean_k, clea
 
 def splice_decode_attn(shape: SpliceShape, call: SpliceCall, cell_LW, q, clean_k, clean_v, donor_k,
                        donor_v, gen_k, gen_v, out, lse, workspace, stream=None) -> None:
-    import torch
     lib = load_library()
-    C, Hq, Hkv, D = shape.n_cells, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    dt = _torch_dtype(shape)
-    n_prompt = Hkv * shape.prompt_len * D
-    qp, dev = _dev_ptr(q, "q", C * Hq * D, dt)
-    ck, _ = _dev_ptr(clean_k, "clean_k", n_prompt, dt, dev)
-    cv, _ = _dev_ptr(clean_v, "clean_v", n_prompt, dt, dev)
-    dk, dv = _donors(shape, donor_k, donor_v, dt, n_prompt, dev)
-    gk, _ = _dev_ptr(gen_k, "gen_k", C * Hkv * shape.gen_capacity * D, dt, dev)
-    gv, _ = _dev_ptr(gen_v, "gen_v", C * Hkv * shape.gen_capacity * D, dt, dev)
-    op, _ = _dev_ptr(out, "out", C * Hq * D, torch.float32, dev)
-    lp, _ = _dev_ptr(lse, "lse", C * Hq, torch.float32, dev)
-    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev)
+    dev, ptrs = _attn_ptrs(shape, q, clean_k, clean_v, donor_k, donor_v, gen_k, gen_v, out, lse)
+    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev[1])
     wbytes = workspace.numel() * workspace.element_size()
-    lw, lwp = _cells(cell_LW, C)
-    _check(lib.splice_decode_attn(ctypes.byref(shape), ctypes.byref(call), lwp, qp, ck, cv, dk, dv, gk, gv,
-                                  op, lp, wp, wbytes, _stream_ptr(stream, dev)), "splice_decode_attn")
+    lw, lwp = _cells(cell_LW, shape.n_cells)
+    _check(lib.splice_decode_attn(ctypes.byref(shape), ctypes.byref(call), lwp, *ptrs, wp, wbytes,
+                                  _stream_ptr(stream, dev[1])), "splice_decode_attn")
 
 
 def splice_decode_attn_noalloc(shape: SpliceShape, call: SpliceCall, cell_LW, q, clean_k, clean_v, donor_k,
                                donor_v, gen_k, gen_v, out, lse, stream=None) -> None:
     """splice_decode_attn with the library's own per-GPU workspace array
     (no workspace argument, nothing allocated)."""
-    import torch
     lib = load_library()
-    C, Hq, Hkv, D = shape.n_cells, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    dt = _torch_dtype(shape)
-    n_prompt = Hkv * shape.prompt_len * D
-    qp, dev = _dev_ptr(q, "q", C * Hq * D, dt)
-    ck, _ = _dev_ptr(clean_k, "clean_k", n_prompt, dt, dev)
-    cv, _ = _dev_ptr(clean_v, "clean_v", n_prompt, dt, dev)
-    dk, dv = _donors(shape, donor_k, donor_v, dt, n_prompt, dev)
-    gk, _ = _dev_ptr(gen_k, "gen_k", C * Hkv * shape.gen_capacity * D, dt, dev)
-    gv, _ = _dev_ptr(gen_v, "gen_v", C * Hkv * shape.gen_capacity * D, dt, dev)
-    op, _ = _dev_ptr(out, "out", C * Hq * D, torch.float32, dev)
-    lp, _ = _dev_ptr(lse, "lse", C * Hq, torch.float32, dev)
-    lw, lwp = _cells(cell_LW, C)
-    _check(lib.splice_decode_attn_noalloc(ctypes.byref(shape), ctypes.byref(call), lwp, qp, ck, cv, dk, dv, gk, gv,
-                                          op, lp, _stream_ptr(stream, dev)), "splice_decode_attn_noalloc")
+    dev, ptrs = _attn_ptrs(shape, q, clean_k, clean_v, donor_k, donor_v, gen_k, gen_v, out, lse)
+    lw, lwp = _cells(cell_LW, shape.n_cells)
+    _check(lib.splice_decode_attn_noalloc(ctypes.byref(shape), ctypes.byref(call), lwp, *ptrs,
+                                          _stream_ptr(stream, dev[1])), "splice_decode_attn_noalloc")
 
 
 def _steps(cell_step, n_cells: int):
-    a = np.ascontiguousarray(np.asarray(cell_step, dtype=np.int32).reshape(-1))
-    if a.shape[0] != n_cells:
-        raise ValueError(f"cell_step has {a.shape[0]} entries, shape says {n_cells} cells")
-    return a, a.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
+    return _host_i32(cell_step, n_cells, 1, "cell_step", "entries")
 
 
 def splice_decode_step(shape: SpliceShape, call: SpliceCall, cell_LW, cell_step, q, k_new, v_new, clean_k,
@@ -302,27 +316,16 @@ def splice_decode_step(shape: SpliceShape, call: SpliceCall, cell_LW, cell_step,
     Appends ``k_new[c]``, ``v_new[c]`` ([C, Hkv, D]) as row ``cell_step[c]`` of the
     cell's generated caches, then attends as ``splice_decode_attn`` at that step.
     """
-    import torch
     lib = load_library()
-    C, Hq, Hkv, D = shape.n_cells, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    dt = _torch_dtype(shape)
-    n_prompt = Hkv * shape.prompt_len * D
-    qp, dev = _dev_ptr(q, "q", C * Hq * D, dt)
-    kn, _ = _dev_ptr(k_new, "k_new", C * Hkv * D, dt, dev)
-    vn, _ = _dev_ptr(v_new, "v_new", C * Hkv * D, dt, dev)
-    ck, _ = _dev_ptr(clean_k, "clean_k", n_prompt, dt, dev)
-    cv, _ = _dev_ptr(clean_v, "clean_v", n_prompt, dt, dev)
-    dk, dv = _donors(shape, donor_k, donor_v, dt, n_prompt, dev)
-    gk, _ = _dev_ptr(gen_k, "gen_k", C * Hkv * shape.gen_capacity * D, dt, dev)
-    gv, _ = _dev_ptr(gen_v, "gen_v", C * Hkv * shape.gen_capacity * D, dt, dev)
-    op, _ = _dev_ptr(out, "out", C * Hq * D, torch.float32, dev)
-    lp, _ = _dev_ptr(lse, "lse", C * Hq, torch.float32, dev)
-    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev)
+    dev, ptrs = _attn_ptrs(shape, q, clean_k, clean_v, donor_k, donor_v, gen_k, gen_v, out, lse)
+    C, n_new, dt = shape.n_cells, shape.n_cells * shape.n_kv_heads * shape.head_dim, _torch_dtype(shape)
+    kn, vn = _ptr(k_new, "k_new", n_new, dt, dev), _ptr(v_new, "v_new", n_new, dt, dev)
+    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev[1])
     wbytes = workspace.numel() * workspace.element_size()
     lw, lwp = _cells(cell_LW, C)
     st, stp = _steps(cell_step, C)
-    _check(lib.splice_decode_step(ctypes.byref(shape), ctypes.byref(call), lwp, stp, qp, kn, vn, ck, cv, dk, dv,
-                                  gk, gv, op, lp, wp, wbytes, _stream_ptr(stream, dev)), "splice_decode_step")
+    _check(lib.splice_decode_step(ctypes.byref(shape), ctypes.byref(call), lwp, stp, ptrs[0], kn, vn, *ptrs[1:], wp,
+                                  wbytes, _stream_ptr(stream, dev[1])), "splice_decode_step")
 
 
 def splice_decode_forked(shape: SpliceShape, call: SpliceCall, cell_LW, trunk: int, q, clean_k, clean_v,
@@ -330,21 +333,10 @@ def splice_decode_forked(shape: SpliceShape, call: SpliceCall, cell_LW, trunk: i
     """Attention of a forked sweep: cell ``trunk`` is the clean run; a cell that
     has diverged reads its generated rows below its onset W from the trunk, and
     a cell that has not takes the trunk's out and lse."""
-    import torch
     lib = load_library()
-    C, Hq, Hkv, D = shape.n_cells, shape.n_q_heads, shape.n_kv_heads, shape.head_dim
-    dt = _torch_dtype(shape)
-    n_prompt = Hkv * shape.prompt_len * D
-    qp, dev = _dev_ptr(q, "q", C * Hq * D, dt)
-    ck, _ = _dev_ptr(clean_k, "clean_k", n_prompt, dt, dev)
-    cv, _ = _dev_ptr(clean_v, "clean_v", n_prompt, dt, dev)
-    dk, dv = _donors(shape, donor_k, donor_v, dt, n_prompt, dev)
-    gk, _ = _dev_ptr(gen_k, "gen_k", C * Hkv * shape.gen_capacity * D, dt, dev)
-    gv, _ = _dev_ptr(gen_v, "gen_v", C * Hkv * shape.gen_capacity * D, dt, dev)
-    op, _ = _dev_ptr(out, "out", C * Hq * D, torch.float32, dev)
-    lp, _ = _dev_ptr(lse, "lse", C * Hq, torch.float32, dev)
-    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev)
+    dev, ptrs = _attn_ptrs(shape, q, clean_k, clean_v, donor_k, donor_v, gen_k, gen_v, out, lse)
+    wp, _ = _dev_ptr(workspace, "workspace", None, None, dev[1])
     wbytes = workspace.numel() * workspace.element_size()
-    lw, lwp = _cells(cell_LW, C)
-    _check(lib.splice_decode_forked(ctypes.byref(shape), ctypes.byref(call), lwp, int(trunk), qp, ck, cv, dk, dv,
-                                    gk, gv, op, lp, wp, wbytes, _stream_ptr(stream, dev)), "splice_decode_forked")
+    lw, lwp = _cells(cell_LW, shape.n_cells)
+    _check(lib.splice_decode_forked(ctypes.byref(shape), ctypes.byref(call), lwp, int(trunk), *ptrs, wp, wbytes,
+                                    _stream_ptr(stream, dev[1])), "splice_decode_forked")
