@@ -755,27 +755,6 @@ struct Fused {
     static_assert(ROWS == NW * 16 * RB, "host and device agree on the row groups");
 };
 
-// The prompt slots 0 .. n_p - 1 (n_p <= B) of one (row, four outputs) in one
-// round of loads: M over the slots and this item's own maximum Mg, the ZERO
-// term, then the slots folded in order (the fixed fold order).
-template <int D, int G, int B>
-__device__ __forceinline__ void merge_slots_once(const AttnArgs &a, __amdgpu_buffer_rsrc_t r, uint32_t sbase, int h,
-                                                 int d, int nz, float Mg, float &M, float &Ls, f32x4_t &O) {
-    f32x4_t ok[B];
-    float mk[B], lk[B], wk[B];
-#pragma unroll
-    for (int j = 0; j < B; ++j)
-        if (j < a.n_p) load_pslot<D, G, true>(r, sbase + (uint32_t)j * a.p_slot_bytes, h, d, ok[j], mk[j], lk[j], wk[j]);
-#pragma unroll
-    for (int j = 0; j < B; ++j)
-        if (j < a.n_p) M = fmaxf(M, mk[j]);
-    M = fmaxf(M, Mg);
-    if (nz > 0) Ls = (float)nz * fast_exp2(-M);
-#pragma unroll
-    for (int j = 0; j < B; ++j)
-        if (j < a.n_p) fold_pslot<true>(mk[j], lk[j], wk[j], ok[j], M, Ls, O);
-}
-
 template <int D, int G>
 struct FusedLds {
     static constexpr int NW = Fused<D>::NW;
@@ -905,6 +884,13 @@ __device__ int fused_prompt_item(const AttnArgs &a, int item, char *lds, int *s_
 // partials are combined, so their latency overlaps the LDS work.  Fold
 // order (fixed, as in combine_cells): the ZERO term, the prompt slots in
 // order, this item's slot; each output is folded exactly as there.
+//
+// With more than 8 slots the rows' records (m, l, w) would not fit beside the
+// outputs in registers: each is loaded once by the work group and read from
+// LDS.  The chain of sc1 round trips bounds it; against loading four outputs
+// and a record a slot per thread, at 16 slots: 4 cells, 4096 keys 24.4 -> 19.5
+// us a call, 16 cells, 8192 keys 30.5 -> 26.3, D = 256, 48 cells, 4096 keys
+// 29.8 -> 24.9.
 template <int D, int G, int NW, int B, int U>
 __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const WaveState<D> &S, char *buf, int wpp,
                                                    int n_pairs, int c0, int g) {
@@ -913,6 +899,8 @@ __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const Wave
     constexpr int NT = NW * 64;
     constexpr int UPR = D / 8;       // units per (cell, q head)
     constexpr int UPG = G * UPR;     // units per (cell, KV head)
+    constexpr bool STAGED = B > 8;
+    constexpr int RECS = STAGED ? (NW * G * B + NT - 1) / NT : 1;   // records a thread loads
     const __amdgpu_buffer_rsrc_t r = part_rsrc(a);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int col = lane & 15, quad = lane >> 4;
@@ -920,6 +908,17 @@ __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const Wave
     float *s_o = reinterpret_cast<float *>(buf);   // [NW][G][D]
     float *s_m = s_o + NW * G * D;                  // [NW][G]
     float *s_l = s_m + NW * G;                      // [NW][G]
+    f32x4_t *s_rec = reinterpret_cast<f32x4_t *>(s_l + NW * G);   // [pair][G][B] (STAGED)
+    static_assert((NW * G * (D + 2) * 4) % 16 == 0, "records are 16-byte aligned");
+    static_assert(!STAGED || NW * G * (D + 2) * 4 + NW * G * B * 16 <= 3 * kRowBlock * kMaxSlots * 4, "fits FusedLds");
+    f32x4_t rec[RECS];
+    if constexpr (STAGED) {
+        static_for<0, RECS>([&](auto i) {
+            const int t = min(tid + (int)i * NT, n_pairs * G * B - 1);
+            const int q = t / (G * B), h = t / B % G, k = min(t % B, a.n_p - 1);
+            rec[i] = part_load4(r, pslot_off(a, a.gorder[c0 + q], g, k) + SL::m(h));
+        });
+    }
     // the waves' partials into LDS (every wave is done with its V^T tile)
     if (col < G) {
         static_for<0, W::NDT>([&](auto t) {
@@ -932,7 +931,7 @@ __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const Wave
     }
     for (int e0 = 0; e0 < total; e0 += NT * U) {
         u32x4_t ok[U][B];   // eight fp16 outputs
-        float mk[U][B], lk[U][B], wk[U][B];
+        float mk[U][STAGED ? 1 : B], lk[U][STAGED ? 1 : B], wk[U][STAGED ? 1 : B];
         int pe[U], he[U], de[U];
         static_for<0, U>([&](auto u) {
             const int e = min(e0 + (int)u * NT + tid, total - 1);   // past the end: repeat a valid unit
@@ -941,24 +940,33 @@ __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const Wave
             const int r8 = e % UPR;
             de[u] = 32 * (r8 >> 2) + 4 * (r8 & 3);
             const uint32_t sbase = pslot_off(a, a.gorder[c0 + pe[u]], g, 0);
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
+            static_for<0, B>([&](auto j) {
                 if (j < a.n_p) {
                     const uint32_t off = sbase + (uint32_t)j * a.p_slot_bytes;
                     ok[u][j] = __builtin_amdgcn_raw_buffer_load_b128(r, off + SL::o(he[u], de[u]), 0, kSc1);
-                    const f32x4_t mlw = part_load4(r, off + SL::m(he[u]));
-                    mk[u][j] = mlw.x;
-                    lk[u][j] = mlw.y;
-                    wk[u][j] = mlw.z;
+                    if constexpr (!STAGED) {
+                        const f32x4_t mlw = part_load4(r, off + SL::m(he[u]));
+                        mk[u][j] = mlw.x;
+                        lk[u][j] = mlw.y;
+                        wk[u][j] = mlw.z;
+                    }
                 }
-            }
+            });
         });
+        if constexpr (STAGED) {
+            if (e0 == 0)
+                static_for<0, RECS>([&](auto i) {
+                    const int t = tid + (int)i * NT;
+                    if (t < n_pairs * G * B) s_rec[t] = rec[i];
+                });
+        }
         __syncthreads();   // the staged partials are visible (first round); no-op ordering after
         static_for<0, U>([&](auto u) {
             const int e = e0 + (int)u * NT + tid;
             const int cq = a.gorder[c0 + pe[u]];
             if (e < total) {
                 const int h = he[u], d0 = de[u], d1 = d0 + 16, w0 = pe[u] * wpp;
+                const f32x4_t *rc = s_rec + (pe[u] * G + h) * B;
                 // this item's partial: its waves combined
                 float Mg = -INFINITY;
 #pragma unroll
@@ -979,20 +987,33 @@ __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const Wave
                 }
                 const int nz = zero_slots(a, cq);
                 float M = nz > 0 ? 0.f : -INFINITY;
-#pragma unroll
-                for (int j = 0; j < B; ++j)
-                    if (j < a.n_p) M = fmaxf(M, mk[u][j]);
+                static_for<0, B>([&](auto j) {
+                    if (j < a.n_p) {
+                        if constexpr (STAGED) M = fmaxf(M, rc[j].x);
+                        else M = fmaxf(M, mk[u][j]);
+                    }
+                });
                 M = fmaxf(M, Mg);
                 float Ls = nz > 0 ? (float)nz * fast_exp2(-M) : 0.f, Ls1 = Ls;
                 f32x4_t O0 = {0.f, 0.f, 0.f, 0.f}, O1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int j = 0; j < B; ++j) {
+                static_for<0, B>([&](auto j) {
                     if (j < a.n_p) {
+                        float m, l, w;
+                        if constexpr (STAGED) {
+                            const f32x4_t mlw = rc[j];
+                            m = mlw.x;
+                            l = mlw.y;
+                            w = mlw.z;
+                        } else {
+                            m = mk[u][j];
+                            l = lk[u][j];
+                            w = wk[u][j];
+                        }
                         const f32x8_t v = __builtin_convertvector(__builtin_bit_cast(h16x8_t, ok[u][j]), f32x8_t);
-                        fold_pslot<true>(mk[u][j], lk[u][j], wk[u][j], f32x4_t{v[0], v[1], v[2], v[3]}, M, Ls, O0);
-                        fold_pslot<true>(mk[u][j], lk[u][j], wk[u][j], f32x4_t{v[4], v[5], v[6], v[7]}, M, Ls1, O1);
+                        fold_pslot<true>(m, l, w, f32x4_t{v[0], v[1], v[2], v[3]}, M, Ls, O0);
+                        fold_pslot<true>(m, l, w, f32x4_t{v[4], v[5], v[6], v[7]}, M, Ls1, O1);
                     }
-                }
+                });
                 fold_slot(Mg, Lg, Og0, M, Ls, O0);   // this item's slot, a.n_p, comes last
                 fold_slot(Mg, Lg, Og1, M, Ls1, O1);
                 write_row(a, cq, g * G + h, d0, D, M, Ls, O0);
@@ -1096,21 +1117,18 @@ __device__ int fused_gen_item(const AttnArgs &a, int item, char *lds, int *s_lis
     if (ready) {
         if (a.n_p <= 8) {
             gen_merge_in_place<D, G, NW, 8, 1>(a, S, lds, wpp, n_pairs, c0, g);
-        } else {
-        waves_merge<D, G, NW>(S, lds, wpp, n_pairs, [&](int q, int h, int d, float Mg, float Lg, f32x4_t Og) {
-            const int cq = a.gorder[c0 + q];
-            const uint32_t sbase = pslot_off(a, cq, g, 0);
-            const int nz = zero_slots(a, cq);
-            float M = nz > 0 ? 0.f : -INFINITY;
-            float Ls = 0.f;
-            f32x4_t O = {0.f, 0.f, 0.f, 0.f};
-            if (a.n_p <= 8) {
-                merge_slots_once<D, G, 8>(a, r, sbase, h, d, nz, Mg, M, Ls, O);
-            } else if (a.n_p <= 16) {
-                merge_slots_once<D, G, 16>(a, r, sbase, h, d, nz, Mg, M, Ls, O);
-            } else {
+        } else if (a.n_p <= splice::kWideMaxChunks) {
+            gen_merge_in_place<D, G, NW, splice::kWideMaxChunks, 1>(a, S, lds, wpp, n_pairs, c0, g);
+        } else {   // more chunks than a default cut makes
+            waves_merge<D, G, NW>(S, lds, wpp, n_pairs, [&](int q, int h, int d, float Mg, float Lg, f32x4_t Og) {
                 using SL = Slot<D, G, true>;
                 constexpr int B = 8;
+                const int cq = a.gorder[c0 + q];
+                const uint32_t sbase = pslot_off(a, cq, g, 0);
+                const int nz = zero_slots(a, cq);
+                float M = nz > 0 ? 0.f : -INFINITY;
+                float Ls = 0.f;
+                f32x4_t O = {0.f, 0.f, 0.f, 0.f};
                 for (int k = 0; k < a.n_p; ++k)
                     M = fmaxf(M, part_load1(r, sbase + (uint32_t)k * a.p_slot_bytes + SL::m(h)));
                 M = fmaxf(M, Mg);
@@ -1126,10 +1144,9 @@ __device__ int fused_gen_item(const AttnArgs &a, int item, char *lds, int *s_lis
                     for (int j = 0; j < B; ++j)
                         if (k0 + j < a.n_p) fold_pslot<true>(mk[j], lk[j], wk[j], ok[j], M, Ls, O);
                 }
-            }
-            fold_slot(Mg, Lg, Og, M, Ls, O);   // this item's slot, a.n_p, comes last
-            write_row(a, cq, g * G + h, d, D, M, Ls, O);
-        });
+                fold_slot(Mg, Lg, Og, M, Ls, O);   // this item's slot, a.n_p, comes last
+                write_row(a, cq, g * G + h, d, D, M, Ls, O);
+            });
         }
         if ((int)threadIdx.x < n_pairs)
             __hip_atomic_store(a.counters + (int)a.gorder[c0 + threadIdx.x] * a.Hkv + g, 0, __ATOMIC_RELAXED,
