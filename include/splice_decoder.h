@@ -33,6 +33,15 @@ SPLICE_API int32_t splice_decoder_norm(const float *x, const float *mean_sq, con
                                        int32_t d, float eps, int32_t packed, void *stream);
 
 /*
+ * splice_decoder_residual, the mean of the squares and splice_decoder_norm at once, d at most
+ * SPLICE_ADD_NORM_MAX_D.  The squares are added in the order in which PyTorch adds rows of 256 to 7680 values when
+ * there are at least eight; for other sizes the mean is as accurate but may differ in its last bit.
+ */
+#define SPLICE_ADD_NORM_MAX_D 8192
+SPLICE_API int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, int32_t rows,
+                                           int32_t d, float eps, int32_t assign, int32_t packed, void *stream);
+
+/*
  * tab [rows][head_dim / 2] = (cos, sin) of position * theta^(-2 i / head_dim),
  * the angle computed in 64 bits.  Positions: pos (device, rows doubles), or
  * with pos == NULL prompt_len + max(step, 0) of the host int32 cell_step.

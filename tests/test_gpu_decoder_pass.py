@@ -132,6 +132,36 @@ def test_norm_rounds_as_the_operations():
         assert torch.equal(h, decode.rms_norm(x + delta.float(), gain, 1e-6).bfloat16())
 
 
+# the smallest and largest sizes the pass takes it at, units that fill the last
+# round in part, and sizes beyond, which it does not take: there the operation
+# adds in another order and the mean differs by a few ulp
+@pytest.mark.parametrize("C,d", [(8, 256), (9, 264), (128, 1032), (8, 2560), (130, 4096), (256, 7680), (8, 7672), (1, 8), (3, 8192),
+                                 (256, 8184)])
+def test_add_norm_adds_as_the_mean(C, d):
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x, delta = torch.randn(C, d, generator=g, device="cuda"), torch.randn(C, d, generator=g, device="cuda").bfloat16()
+    gain = (1 + 0.2 * torch.randn(d, generator=g, device="cuda")).bfloat16()
+    lib = decode._library()
+    for assign in (0, 1):
+        want_x = delta.float() if assign else x + delta.float()
+        want = decode.rms_norm(want_x, gain, 1e-6).bfloat16()
+        for packed in (0, 1) if d % 32 == 0 else (0,):
+            rows = (C + 15) // 16 * 16
+            y, h = x.clone(), torch.zeros(rows, d, device="cuda", dtype=torch.bfloat16)
+            gc.announce(f"add_norm {C}x{d} assign={assign} packed={packed}")
+            assert lib.splice_decoder_add_norm(y.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), C, d, 1e-6,
+                                               assign, packed, None) == 0
+            got = h.view(d // 32, rows // 16, 16, 32).permute(1, 2, 0, 3).reshape(rows, d) if packed else h
+            assert torch.equal(y, want_x)
+            if C >= 8 and 256 <= d <= 7680:
+                assert torch.equal(got[:C], want)
+            else:   # another order of the sum: one bf16 step at most
+                assert ((got[:C].float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs()).all()
+            assert not got[C:].any()
+    assert lib.splice_decoder_add_norm(x.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), C, 8200, 1e-6, 0, 0,
+                                       None) == sp.SPLICE_EUNSUPPORTED
+
+
 @pytest.mark.parametrize("rows,vocab", [(1, 1), (3, 257), (130, 1023), (7, 70001)])
 def test_greedy_is_argmax(rows, vocab):
     g = torch.Generator(device="cuda").manual_seed(rows)
