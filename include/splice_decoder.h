@@ -34,12 +34,12 @@ SPLICE_API int32_t splice_decoder_norm(const float *x, const float *mean_sq, con
 
 /*
  * splice_decoder_residual, the mean of the squares and splice_decoder_norm at once, d at most
- * SPLICE_ADD_NORM_MAX_D.  The squares are added in the order in which PyTorch adds rows of 256 to 7680 values when
+ * SPLICE_ADD_NORM_MAX_D: h plain, h_packed packed, either may be NULL.  The squares are added in the order in which PyTorch adds rows of 256 to 7680 values when
  * there are at least eight; for other sizes the mean is as accurate but may differ in its last bit.
  */
 #define SPLICE_ADD_NORM_MAX_D 8192
-SPLICE_API int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, int32_t rows,
-                                           int32_t d, float eps, int32_t assign, int32_t packed, void *stream);
+SPLICE_API int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, void *h_packed,
+                                           int32_t rows, int32_t d, float eps, int32_t assign, void *stream);
 
 /*
  * tab [rows][head_dim / 2] = (cos, sin) of position * theta^(-2 i / head_dim),
@@ -53,11 +53,21 @@ SPLICE_API int32_t splice_decoder_rope_table(float *tab, const double *pos, cons
 SPLICE_API int32_t splice_decoder_rope(void *q, void *k, const float *tab, int32_t rows, int32_t n_q, int32_t n_kv,
                                        int32_t head_dim, void *stream);
 
-/* dst = bf16(src), n values, a multiple of 8. */
-SPLICE_API int32_t splice_decoder_round(const float *src, void *dst, int64_t n, void *stream);
+/* dst = bf16(src), [rows][d], d a multiple of 8 (packed: of 32, and packed as splice_decoder_norm's h). */
+SPLICE_API int32_t splice_decoder_round(const float *src, void *dst, int32_t rows, int32_t d, int32_t packed,
+                                        void *stream);
 
-/* act = bf16(bf16(silu(gate)) * up), bf16, n values, a multiple of 8. */
-SPLICE_API int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int64_t n, void *stream);
+/* act = bf16(bf16(silu(gate)) * up), bf16, [rows][d] as splice_decoder_round; act may be gate unless packed. */
+SPLICE_API int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int32_t rows, int32_t d,
+                                       int32_t packed, void *stream);
+
+/*
+ * y [rows][n] = bf16(x . w [k][n]), bf16, x packed, fp32 sums in the order of k: k a multiple of 128, n of 8.
+ * splice_decoder_product_takes: whether a pass uses it (1) or leaves the product to the library (0).
+ */
+SPLICE_API int32_t splice_decoder_product_takes(int32_t rows, int32_t k, int32_t n);
+SPLICE_API int32_t splice_decoder_product(const void *x, const void *w, void *y, int32_t rows, int32_t k, int32_t n,
+                                          void *stream);
 
 /*
  * logits [rows][vocab] = float(bf16(h . w [d][vocab])), bf16 inputs, h packed

@@ -63,8 +63,8 @@ __global__ __launch_bounds__(kDecThreads) void norm_kernel(const float *x, const
 // neighbouring lanes; times 1 / d.  At 8 rows of 2560 values 4.2 us a
 // norm, before 13.0 (4.0 + 5.8 + 3.2); at 128 of 4096 5.2, before 17.8.
 __global__ __launch_bounds__(kDecThreads) void add_norm_kernel(float *x, const __bf16 *delta, const __bf16 *gain,
-                                                               __bf16 *h, int rows, int d, float inv_d, float eps,
-                                                               int assign, int packed) {
+                                                               __bf16 *h, __bf16 *hp, int rows, int d, float inv_d,
+                                                               float eps, int assign) {
     constexpr int U = SPLICE_ADD_NORM_MAX_D / (8 * kDecThreads);   // units of eight values a thread
     __shared__ f32x4_t s_sq[SPLICE_ADD_NORM_MAX_D / 4];
     __shared__ float s_mean;
@@ -102,7 +102,11 @@ __global__ __launch_bounds__(kDecThreads) void add_norm_kernel(float *x, const _
     const float r = (float)(1.0 / sqrt((double)(s_mean + eps)));   // correctly rounded, as the operation's
     static_for<0, U>([&](auto i) {
         const int u = tid + (int)i * kDecThreads;
-        if (u < n) store_bf16x8(h + norm_at(row, 8 * u, rows, d, packed), v[i] * r * g[i]);
+        if (u < n) {
+            const f32x8v_t y = v[i] * r * g[i];
+            if (h) store_bf16x8(h + norm_at(row, 8 * u, rows, d, 0), y);
+            if (hp) store_bf16x8(hp + norm_at(row, 8 * u, rows, d, 1), y);
+        }
     });
 }
 
@@ -122,7 +126,6 @@ __global__ __launch_bounds__(kDecThreads) void rope_table_kernel(float2 *tab, co
 // A unit is four pairs (i, i + D / 2) of one (row, head).
 __global__ __launch_bounds__(kDecThreads) void rope_kernel(__bf16 *q, __bf16 *k, const float2 *tab, int rows, int Hq,
                                                            int Hkv, int D) {
-    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     const int half = D / 2, per = half / 4, heads = Hq + Hkv;
     const int u = blockIdx.x * kDecThreads + threadIdx.x;
     if (u >= rows * heads * per) return;
@@ -141,13 +144,19 @@ __global__ __launch_bounds__(kDecThreads) void rope_kernel(__bf16 *q, __bf16 *k,
     *reinterpret_cast<bf16x4_t *>(p + half) = __builtin_convertvector(y2, bf16x4_t);
 }
 
-__global__ __launch_bounds__(kDecThreads) void round_kernel(const float *src, __bf16 *dst, int64_t units) {
+// Where unit u (eight values) of [rows][d] goes.
+__device__ __forceinline__ int64_t unit_at(int64_t u, int rows, int d, int packed) {
+    return packed ? norm_at((int)(u / (d / 8)), 8 * (int)(u % (d / 8)), rows, d, 1) : 8 * u;
+}
+
+__global__ __launch_bounds__(kDecThreads) void round_kernel(const float *src, __bf16 *dst, int64_t units, int rows, int d,
+                                                            int packed) {
     const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
-    if (u < units) store_bf16x8(dst + 8 * u, load_f32x8(src + 8 * u));
+    if (u < units) store_bf16x8(dst + unit_at(u, rows, d, packed), load_f32x8(src + 8 * u));
 }
 
 __global__ __launch_bounds__(kDecThreads) void silu_kernel(const __bf16 *gate, const __bf16 *up, __bf16 *act,
-                                                           int64_t units) {
+                                                           int64_t units, int rows, int d, int packed) {
     const int64_t u = (int64_t)blockIdx.x * kDecThreads + threadIdx.x;
     if (u >= units) return;
     const f32x8v_t g = load_bf16x8(gate + 8 * u), w = load_bf16x8(up + 8 * u);
@@ -156,7 +165,7 @@ __global__ __launch_bounds__(kDecThreads) void silu_kernel(const __bf16 *gate, c
         const float x = g[(int)i];
         o[(int)i] = (float)(__bf16)(x / (1.f + expf(-x))) * w[(int)i];
     });
-    store_bf16x8(act + 8 * u, o);
+    store_bf16x8(act + unit_at(u, rows, d, packed), o);
 }
 
 // ---------------------------------------------------------------- argmax
@@ -262,7 +271,7 @@ void launch_head(HeadArgs a, const HeadPlan &p, float *part, hipStream_t stream)
     a.part = part;
     const int tiles = (a.N + X::COLS - 1) / X::COLS;
     const dim3 grid((unsigned)(p.n_full + (tiles - p.n_full) * p.split), (unsigned)((a.M + 16 * MB - 1) / (16 * MB)));
-    hipLaunchKernelGGL((head_kernel<MB, NS, NB, WN, WM>), grid, dim3(64 * WN * WM), 0, stream, a);
+    hipLaunchKernelGGL((head_kernel<MB, NS, NB, WN, WM, 1, false>), grid, dim3(64 * WN * WM), 0, stream, a);
     if (p.rest > 0)
         hipLaunchKernelGGL(head_sum_kernel, dim3((unsigned)(((int64_t)a.M * p.rest / 4 + 255) / 256)), dim3(256), 0, stream,
                            part, a.y, a.M, a.N, a.N - p.rest, p.split);
@@ -297,13 +306,13 @@ int32_t splice_decoder_norm(const float *x, const float *mean_sq, const void *ga
     return launched();
 }
 
-int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, int32_t rows, int32_t d,
-                                float eps, int32_t assign, int32_t packed, void *stream) {
-    if (!good({x, delta, gain, h})) return SPLICE_EINVAL;
-    if (rows < 1 || d < 8 || d % 8 || d > SPLICE_ADD_NORM_MAX_D || (packed && d % 32)) return SPLICE_EUNSUPPORTED;
+int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, void *h_packed, int32_t rows,
+                                int32_t d, float eps, int32_t assign, void *stream) {
+    if (!good({x, delta, gain, h ? h : h_packed, h_packed ? h_packed : h})) return SPLICE_EINVAL;
+    if (rows < 1 || d < 8 || d % 8 || d > SPLICE_ADD_NORM_MAX_D || (h_packed && d % 32)) return SPLICE_EUNSUPPORTED;
     hipLaunchKernelGGL(add_norm_kernel, dim3((unsigned)rows), dim3(kDecThreads), 0, (hipStream_t)stream, x,
-                       (const __bf16 *)delta, (const __bf16 *)gain, (__bf16 *)h, rows, d, (float)(1.0 / d), eps, assign,
-                       packed);
+                       (const __bf16 *)delta, (const __bf16 *)gain, (__bf16 *)h, (__bf16 *)h_packed, rows, d,
+                       (float)(1.0 / d), eps, assign);
     return launched();
 }
 
@@ -330,19 +339,57 @@ int32_t splice_decoder_rope(void *q, void *k, const float *tab, int32_t rows, in
     return launched();
 }
 
-int32_t splice_decoder_round(const float *src, void *dst, int64_t n, void *stream) {
+// [rows][d] as units of eight values, packed in steps of 32.
+static bool good_rows(int32_t rows, int32_t d, int32_t packed) {
+    return rows >= 1 && d >= 8 && d % 8 == 0 && !(packed && d % 32);
+}
+
+int32_t splice_decoder_round(const float *src, void *dst, int32_t rows, int32_t d, int32_t packed, void *stream) {
     if (!good({src, dst})) return SPLICE_EINVAL;
-    if (n < 8 || n % 8 || n > kMostValues) return SPLICE_EUNSUPPORTED;
-    hipLaunchKernelGGL(round_kernel, dim3(blocks_of(n / 8)), dim3(kDecThreads), 0, (hipStream_t)stream, src,
-                       (__bf16 *)dst, n / 8);
+    const int64_t units = (int64_t)rows * (d / 8);
+    if (!good_rows(rows, d, packed) || units > kMostValues / 8) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(round_kernel, dim3(blocks_of(units)), dim3(kDecThreads), 0, (hipStream_t)stream, src, (__bf16 *)dst,
+                       units, rows, d, packed);
     return launched();
 }
 
-int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int64_t n, void *stream) {
-    if (!good({gate, up, act})) return SPLICE_EINVAL;
-    if (n < 8 || n % 8 || n > kMostValues) return SPLICE_EUNSUPPORTED;
-    hipLaunchKernelGGL(silu_kernel, dim3(blocks_of(n / 8)), dim3(kDecThreads), 0, (hipStream_t)stream,
-                       (const __bf16 *)gate, (const __bf16 *)up, (__bf16 *)act, n / 8);
+int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int32_t rows, int32_t d, int32_t packed,
+                            void *stream) {
+    if (!good({gate, up, act}) || (packed && (act == gate || act == up))) return SPLICE_EINVAL;
+    const int64_t units = (int64_t)rows * (d / 8);
+    if (!good_rows(rows, d, packed) || units > kMostValues / 8) return SPLICE_EUNSUPPORTED;
+    hipLaunchKernelGGL(silu_kernel, dim3(blocks_of(units)), dim3(kDecThreads), 0, (hipStream_t)stream,
+                       (const __bf16 *)gate, (const __bf16 *)up, (__bf16 *)act, units, rows, d, packed);
+    return launched();
+}
+
+// A layer's product in one round of small tiles. Each work group sums all of K
+// in order, as the library's kernels for 64 and 128 rows do (the same bits: no
+// split over K), so a product takes the time of one chain over K. The library
+// takes 64 or 128 rows at once there and leaves most compute units idle; tiles
+// of 32 rows and 64 columns fill the GPU (us, library against this, 128 rows:
+// K = 4096, 4096 columns 39.2 / 22.6, 2560 columns 40.9 / 23.2, K = 12288, 4096
+// columns 106.5 / 59.5; a barrier every 32 of K instead of every 128: 27.2,
+// 26.5, 70.0).  Other numbers of rows have library tiles that fit (112 rows:
+// 23.3) or sums in another order (96 rows, 2560 columns), fewer columns are
+// split over K there, and more than one round of tiles loses (K = 4096, 12288
+// columns: 42.6 / 68.4).
+using Product = Head<2, 1, 5, 4, 1, 4, true>;
+constexpr int kProductCols = 2048;   // fewer: left to the library
+
+int32_t splice_decoder_product_takes(int32_t rows, int32_t k, int32_t n) {
+    return (rows == 64 || rows == 128) && k >= 128 && k % 128 == 0 && k <= 1 << 20 && n >= kProductCols && n % 8 == 0 &&
+           n <= 1 << 24 && (int64_t)(rows / 32) * ((n + Product::COLS - 1) / Product::COLS) <= compute_units();
+}
+
+int32_t splice_decoder_product(const void *x, const void *w, void *y, int32_t rows, int32_t k, int32_t n, void *stream) {
+    if (!good({x, w, y})) return SPLICE_EINVAL;
+    if (rows < 1 || rows > SPLICE_MAX_CELLS || k < 128 || k % 128 || k > 1 << 20 || n < 8 || n % 8 || n > 1 << 24)
+        return SPLICE_EUNSUPPORTED;
+    const int tiles = (n + Product::COLS - 1) / Product::COLS;
+    const HeadArgs a{(const char *)x, (const char *)w, (float *)y, rows, k, n, tiles, 1, nullptr};
+    hipLaunchKernelGGL((head_kernel<2, 1, 5, 4, 1, 4, true>), dim3((unsigned)tiles, (unsigned)((rows + 31) / 32)), dim3(256),
+                       0, (hipStream_t)stream, a);
     return launched();
 }
 

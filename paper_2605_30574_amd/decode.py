@@ -42,10 +42,12 @@ def _library():
         vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
         for name, args in (("residual", [vp, vp, vp, i64, i32, vp]),
                            ("norm", [vp, vp, vp, vp, i32, i32, ctypes.c_float, i32, vp]),
-                           ("add_norm", [vp, vp, vp, vp, i32, i32, ctypes.c_float, i32, i32, vp]),
+                           ("add_norm", [vp, vp, vp, vp, vp, i32, i32, ctypes.c_float, i32, vp]),
                            ("rope_table", [vp, vp, vp, i32, i32, i32, ctypes.c_double, vp]),
                            ("rope", [vp, vp, vp, i32, i32, i32, i32, vp]),
-                           ("round", [vp, vp, i64, vp]), ("silu", [vp, vp, vp, i64, vp]),
+                           ("round", [vp, vp, i32, i32, i32, vp]),
+                           ("silu", [vp, vp, vp, i32, i32, i32, vp]), ("product_takes", [i32, i32, i32]),
+                           ("product", [vp, vp, vp, i32, i32, i32, vp]),
                            ("head", [vp, vp, vp, i32, i32, i32, vp, ctypes.c_size_t, vp]), ("argmax", [vp, i32, i32, vp, vp, vp])):
             f = getattr(lib, "splice_decoder_" + name)
             f.restype, f.argtypes = i32, args
@@ -190,10 +192,11 @@ class SweepDecoder:
                                          float(m.rope_theta), stream), "splice_decoder_rope_table")
 
         def norm(delta, gain, assign=0, packed=0):
-            """x += delta (the first: x = delta); h = bf16(rms_norm(x)), packed for the head."""
+            """x += delta (the first: x = delta); h = bf16(rms_norm(x)), packed for the head (2: both, packed in hq)."""
             if one_norm:
-                ok(lib.splice_decoder_add_norm(xp, delta.data_ptr(), gain.data_ptr(), hp, C, d, m.rms_eps, assign, packed,
-                                               stream), "splice_decoder_add_norm")
+                ok(lib.splice_decoder_add_norm(xp, delta.data_ptr(), gain.data_ptr(), None if packed == 1 else hp,
+                                               (None, hp, hqp)[packed], C, d, m.rms_eps, assign, stream),
+                   "splice_decoder_add_norm")
                 return
             ok(lib.splice_decoder_residual(xp, delta.data_ptr(), sq.data_ptr(), C * d, assign, stream),
                "splice_decoder_residual")
@@ -201,21 +204,36 @@ class SweepDecoder:
             ok(lib.splice_decoder_norm(xp, mean.data_ptr(), gain.data_ptr(), hp, C, d, m.rms_eps, packed, stream),
                "splice_decoder_norm")
 
+        def own(w):
+            """Whether the library's own product takes this weight."""
+            return one_norm and _dense(w) and lib.splice_decoder_product_takes(C, w.shape[0], w.shape[1]) == 1
+
+        def product(x_packed, w):
+            y = torch.empty((C, w.shape[1]), dtype=bf16, device=dev)
+            ok(lib.splice_decoder_product(x_packed, w.data_ptr(), y.data_ptr(), C, w.shape[0], w.shape[1], stream),
+               "splice_decoder_product")
+            return y
+
+        hq = torch.empty_like(h) if any(own(p["w_q"]) for p in wt["layers"]) else h
+        hqp = hq.data_ptr()
         first = 1
         for l in range(self.N):
             p, c = wt["layers"][l], self.caches[l]
-            norm(delta, p["norm_1"], first)
+            own_q, own_o, own_down = own(p["w_q"]), own(p["w_o"]), own(p["w_down"])
+            norm(delta, p["norm_1"], first, 2 if own_q else 0)
             first = 0
-            q, k, v = h @ p["w_q"], h @ p["w_k"], h @ p["w_v"]
+            q = product(hqp, p["w_q"]) if own_q else h @ p["w_q"]
+            k, v = h @ p["w_k"], h @ p["w_v"]
             ok(lib.splice_decoder_rope(q.data_ptr(), k.data_ptr(), tp, C, Hq, Hkv, D, stream), "splice_decoder_rope")
             S.splice_decode_step(self.shape, self.calls[l], self.lw, st, q, k, v, c["clean_k"], c["clean_v"],
                                  c["donor_k"], c["donor_v"], c["gen_k"], c["gen_v"], self.out, self.lse, self.ws)
-            ok(lib.splice_decoder_round(outp, op, C * Hq * D, stream), "splice_decoder_round")
-            norm(o @ p["w_o"], p["norm_2"])
+            ok(lib.splice_decoder_round(outp, op, C, Hq * D, own_o, stream), "splice_decoder_round")
+            norm(product(op, p["w_o"]) if own_o else o @ p["w_o"], p["norm_2"])
             gate, up = h @ p["w_gate"], h @ p["w_up"]
-            ok(lib.splice_decoder_silu(gate.data_ptr(), up.data_ptr(), gate.data_ptr(), gate.numel(), stream),
+            act = torch.empty_like(gate) if own_down else gate
+            ok(lib.splice_decoder_silu(gate.data_ptr(), up.data_ptr(), act.data_ptr(), C, gate.shape[1], own_down, stream),
                "splice_decoder_silu")
-            delta = gate @ p["w_down"]
+            delta = product(act.data_ptr(), p["w_down"]) if own_down else act @ p["w_down"]
         head = wt["lm_head"]
         vocab = head.shape[1]
         own_head = _dense(head) and d % 32 == 0 and vocab % 8 == 0 and 0 < vocab <= 1 << 24

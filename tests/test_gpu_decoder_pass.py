@@ -72,7 +72,7 @@ def _compare(make, wt, tokens, steps, what, pos=None):
     (1, 32, 32, 8, 2, 1, 64, 1), (16, 96, 160, 136, 4, 2, 64, 2), (17, 256, 416, 1000, 8, 2, 64, 1),
     (33, 320, 96, 264, 4, 4, 128, 2), (65, 128, 512, 520, 4, 2, 256, 1), (128, 512, 768, 4104, 8, 8, 64, 1),
     (129, 224, 352, 264, 4, 2, 64, 1), (256, 256, 64, 512, 2, 1, 64, 1), (24, 1056, 64, 66600, 2, 1, 64, 1),
-    (100, 1056, 64, 66600, 2, 1, 64, 1), (9, 72, 104, 100, 4, 2, 64, 1)])
+    (100, 1056, 64, 66600, 2, 1, 64, 1), (64, 2048, 256, 264, 32, 4, 64, 1), (128, 2056, 2176, 264, 16, 2, 128, 2), (9, 72, 104, 100, 4, 2, 64, 1)])
 def test_fused_pass_keeps_the_bits(C, d, F, V, Hq, Hkv, D, N):
     make, wt, tokens, steps = _decoder(C, d, F, V, Hq, Hkv, D, N)
     _compare(make, wt, tokens, steps, f"C={C} d={d} F={F} V={V} D={D}")
@@ -149,8 +149,8 @@ def test_add_norm_adds_as_the_mean(C, d):
             rows = (C + 15) // 16 * 16
             y, h = x.clone(), torch.zeros(rows, d, device="cuda", dtype=torch.bfloat16)
             gc.announce(f"add_norm {C}x{d} assign={assign} packed={packed}")
-            assert lib.splice_decoder_add_norm(y.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), C, d, 1e-6,
-                                               assign, packed, None) == 0
+            assert lib.splice_decoder_add_norm(y.data_ptr(), delta.data_ptr(), gain.data_ptr(), None if packed else h.data_ptr(),
+                                               h.data_ptr() if packed else None, C, d, 1e-6, assign, None) == 0
             got = h.view(d // 32, rows // 16, 16, 32).permute(1, 2, 0, 3).reshape(rows, d) if packed else h
             assert torch.equal(y, want_x)
             if C >= 8 and 256 <= d <= 7680:
@@ -158,8 +158,29 @@ def test_add_norm_adds_as_the_mean(C, d):
             else:   # another order of the sum: one bf16 step at most
                 assert ((got[:C].float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs()).all()
             assert not got[C:].any()
-    assert lib.splice_decoder_add_norm(x.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), C, 8200, 1e-6, 0, 0,
+    assert lib.splice_decoder_add_norm(x.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), None, C, 8200, 1e-6, 0,
                                        None) == sp.SPLICE_EUNSUPPORTED
+
+
+# one and several row groups, rows and columns that fill the last tile in part,
+# K of one stage, of fewer stages than the ring and of many
+@pytest.mark.parametrize("rows,K,N", [(1, 128, 8), (33, 256, 72), (64, 512, 2048), (128, 4096, 2056), (200, 1408, 136)])
+def test_product(rows, K, N):
+    g = torch.Generator(device="cuda").manual_seed(K + N)
+    x = torch.randn(rows, K, generator=g, device="cuda").bfloat16()
+    w = (torch.randn(K, N, generator=g, device="cuda") * K ** -0.5).bfloat16()
+    pad = (rows + 15) // 16 * 16
+    xp = torch.zeros(pad, K, device="cuda", dtype=torch.bfloat16)
+    xp[:rows] = x
+    xp = xp.view(pad // 16, 16, K // 32, 32).permute(2, 0, 1, 3).contiguous()
+    y = torch.full((rows + 1, N), 7.0, device="cuda", dtype=torch.bfloat16)
+    gc.announce(f"product {rows}x{K}x{N}")
+    lib = decode._library()
+    assert lib.splice_decoder_product(xp.data_ptr(), w.data_ptr(), y.data_ptr(), rows, K, N, None) == 0
+    want = (x.double() @ w.double())
+    bound = 2.0 ** -8 * want.abs() + K * 2.0 ** -24 * (x.double().abs() @ w.double().abs())   # rounding, fp32 sums
+    assert ((y[:rows].double() - want).abs() <= bound).all() and (y[rows] == 7).all()
+    assert lib.splice_decoder_product(xp.data_ptr(), w.data_ptr(), y.data_ptr(), rows, K + 32, N, None) == sp.SPLICE_EUNSUPPORTED
 
 
 @pytest.mark.parametrize("rows,vocab", [(1, 1), (3, 257), (130, 1023), (7, 70001)])
