@@ -8,8 +8,10 @@ pre-norm blocks of grouped-query attention and a gated MLP.  Per layer and
 step the attention -- the current token's K/V appended to each cell's
 generated cache, then single-query attention over the cell's spliced prompt
 and its generated rows -- is one ``splice_decode_step`` launch of this
-library's kernel; the projections, norms, rotary embedding and MLP are plain
-PyTorch operations (library GEMMs), outside the measured hot path.
+library's kernel. Around it, with dense bf16 weights on the GPU, what lies
+between the products, the head, the argmax and the products it has better
+tiles for are this library's kernels too (``include/splice_decoder.h``); the
+other products, and passes with other weights, are PyTorch operations.
 
 Readings of what the paper leaves to the model (the same on the CPU
 reference in ``oracle.decoder``):
