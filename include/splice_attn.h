@@ -149,7 +149,11 @@ SPLICE_API int64_t splice_decode_attn_workspace_bytes(const splice_shape *shape,
  * splice_decode_attn / splice_decode_step: the workspace starts with a
  * 256-byte statistics block (splice_workspace_handovers) and the
  * per-(cell, KV head) arrival counters, which must start at zero; every call
- * re-arms the counters it used, so later calls need no re-initialisation.
+ * re-arms the counters it used, so later calls with the same number of
+ * (cell, KV head) pairs need no re-initialisation.  The partial results lie
+ * right behind the counters of a call's n_cells * n_kv_heads pairs, so a
+ * workspace that is to serve another number of pairs is initialised again
+ * first (its counters lie where a call with fewer left partial results).
  * workspace must be 256-byte aligned and workspace_bytes a multiple of 4.
  */
 SPLICE_API int32_t splice_workspace_init(void *workspace, size_t workspace_bytes, void *stream);
@@ -194,13 +198,14 @@ SPLICE_API int32_t splice_decode_attn(const splice_shape *shape, const splice_ca
  * for callers that cannot call hipMalloc (code under HIP graph capture,
  * serving loops that must not allocate, harnesses that forbid it).  The
  * split-K partials and arrival counters live in a library-owned device
- * array of SPLICE_NOALLOC_WORKSPACE_BYTES bytes, one per GPU, held until
- * the process ends; calls whose splice_decode_attn_workspace_bytes(shape,
+ * array, one per GPU, held until the process ends, in place of a workspace of
+ * SPLICE_NOALLOC_WORKSPACE_BYTES bytes; calls whose splice_decode_attn_workspace_bytes(shape,
  * call) exceeds it return SPLICE_EWORKSPACE before any device work.  The
  * first call on a device takes the array's address and clears it with a
  * fill kernel on `stream` (make that first call outside graph capture);
- * every later call finds the arrival counters at zero, because each call
- * re-arms the counters it uses.  All calls on one GPU share the array:
+ * every later call, of whatever shape, finds the arrival counters at zero:
+ * each call re-arms the counters it uses, and the counters have a block of
+ * their own that no call's partial results reach.  All calls on one GPU share the array:
  * calls that overlap on one GPU (other streams, other threads) race and must
  * be ordered by the caller, e.g. on one stream.  Arguments, results, errors
  * and bits are those of splice_decode_attn (same kernels, same plan).

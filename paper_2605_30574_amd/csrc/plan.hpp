@@ -533,6 +533,24 @@ inline WorkspaceLayout workspace_layout(const splice_shape &sh, int n_slots) {
     return w;
 }
 
+// The no-allocation entry's array, which serves calls of every shape in turn:
+// as a workspace of SPLICE_NOALLOC_WORKSPACE_BYTES, but with a counter block of
+// one size, so that no shape's partial results lie where another shape keeps
+// its counters (which every call must find at zero).  A call whose workspace
+// is within the limit and that has partial results has a slot of 512 bytes or
+// more for each pair, so fewer pairs than the block has counters.
+constexpr int kNoallocPairs = 1 << 16;
+constexpr size_t kNoallocBytes = SPLICE_NOALLOC_WORKSPACE_BYTES + (size_t)kNoallocPairs * 4;
+static_assert(SPLICE_NOALLOC_WORKSPACE_BYTES / 512 <= kNoallocPairs, "a counter for every pair that has a slot");
+
+inline WorkspaceLayout noalloc_layout(const splice_shape &sh, int n_slots) {
+    WorkspaceLayout w = workspace_layout(sh, n_slots);
+    w.counters_bytes = (size_t)kNoallocPairs * 4;
+    w.part_off = w.counters_off + w.counters_bytes;
+    w.total = w.part_off + w.part_bytes;
+    return w;
+}
+
 // Most slots any default-split call on this shape uses.  For n keys the
 // default cut makes at most min(ceil(n / kMinChunk), target) chunks (each
 // chunk is at least n / that many keys long), and that bound grows with n;

@@ -303,12 +303,13 @@ namespace {
 // splice_decode_attn (cell_step == nullptr, trunk < 0: every cell at
 // call->step), splice_decode_step (each cell at cell_step[c], k_new/v_new
 // appended) and splice_decode_forked (trunk >= 0: cells that have not
-// diverged from the trunk by call->step take its result).
+// diverged from the trunk by call->step take its result).  noalloc: the
+// workspace is the library's array of splice::kNoallocBytes.
 int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, const int32_t *cell_LW,
                          const int32_t *cell_step, int trunk, const void *q, const void *k_new, const void *v_new,
                          const void *clean_k, const void *clean_v, const void *donor_k, const void *donor_v,
                          const void *gen_k, const void *gen_v, float *out, float *lse, void *workspace,
-                         size_t workspace_bytes, void *stream) {
+                         size_t workspace_bytes, void *stream, bool noalloc = false) {
     int32_t rc = splice::validate_shape(shape);
     if (rc != SPLICE_OK) return rc;
     const splice_shape &sh = *shape;
@@ -390,10 +391,12 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
     const splice::Residency res =
         splice::bf16_path(sh) ? residency((const void *)kern.items, threads) : splice::Residency();
     splice::AttnPlan plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, g_lo.n_gen == g_hi.n_gen);
-    if (plan.wide && workspace_bytes < splice::workspace_layout(sh, plan.n_slots).total)   // the route with fewer slots
+    if (plan.wide && (noalloc ? (size_t)SPLICE_NOALLOC_WORKSPACE_BYTES : workspace_bytes) <
+                         splice::workspace_layout(sh, plan.n_slots).total)   // the route with fewer slots
         plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, true, false);
     if (plan.n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
-    const splice::WorkspaceLayout wl = splice::workspace_layout(sh, plan.n_slots);
+    const splice::WorkspaceLayout wl =
+        noalloc ? splice::noalloc_layout(sh, plan.n_slots) : splice::workspace_layout(sh, plan.n_slots);
     if (!workspace || !splice::aligned(workspace, 256)) return SPLICE_EWORKSPACE;
     if (workspace_bytes < wl.total) return SPLICE_EWORKSPACE;
 
@@ -515,7 +518,7 @@ namespace {
 // The allocation-free entry point's workspace: one array per GPU, held until
 // the process ends.  In host code `scratch` is only a stand-in for the
 // symbol; its device address comes from hipGetSymbolAddress, once per device.
-static __device__ __align__(256) char scratch[SPLICE_NOALLOC_WORKSPACE_BYTES];
+static __device__ __align__(256) char scratch[splice::kNoallocBytes];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
@@ -523,8 +526,9 @@ void *g_scratch[kMaxDevices];   // device address of `scratch` on each device, s
 
 // The current device's scratch array.  The first call on a device takes its
 // address and clears it with the fill kernel on `stream` (the arrival
-// counters must start at zero; every call re-arms the counters it used, so
-// the array is left zeroed for the next call).
+// counters must start at zero; every call re-arms the counters it used, and no
+// call's partial results lie in the counter block, so the next call of any
+// shape finds them at zero).
 int32_t device_scratch(void *stream, void **ptr) {
     int dev = -1;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return SPLICE_EHIP;
@@ -532,7 +536,7 @@ int32_t device_scratch(void *stream, void **ptr) {
     if (!g_scratch[dev]) {
         void *p = nullptr;
         if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return SPLICE_EHIP;
-        const size_t words = SPLICE_NOALLOC_WORKSPACE_BYTES / 4;
+        const size_t words = splice::kNoallocBytes / 4;
         hipLaunchKernelGGL(fill_kernel, dim3(4096), dim3(kThreads), 0, (hipStream_t)stream, (uint32_t *)p, words);
         if (hipGetLastError() != hipSuccess) return SPLICE_EHIP;
         g_scratch[dev] = p;
@@ -558,7 +562,7 @@ int32_t splice_decode_attn_noalloc(const splice_shape *shape, const splice_call 
     const int32_t rc = device_scratch(stream, &ws);
     if (rc != SPLICE_OK) return rc;
     return decode_attn_impl(shape, call, cell_LW, nullptr, -1, q, nullptr, nullptr, clean_k, clean_v, donor_k,
-                            donor_v, gen_k, gen_v, out, lse, ws, SPLICE_NOALLOC_WORKSPACE_BYTES, stream);
+                            donor_v, gen_k, gen_v, out, lse, ws, splice::kNoallocBytes, stream, true);
 }
 
 int32_t splice_decode_step(const splice_shape *shape, const splice_call *call, const int32_t *cell_LW,

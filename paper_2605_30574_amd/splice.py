@@ -249,7 +249,10 @@ def splice_workspace_handovers(workspace, stream=None) -> int:
 
 
 def new_workspace(shape: SpliceShape, call: Optional[SpliceCall] = None, device="cuda", stream=None):
-    """Allocate (torch) and prepare a workspace for ``shape`` (and ``call``)."""
+    """Allocate (torch) and prepare a workspace for ``shape`` (and ``call``).
+
+    Before it serves a shape with another number of (cell, KV head) pairs it is
+    prepared again (``splice_workspace_init``)."""
     import torch
     nbytes = splice_decode_attn_workspace_bytes(shape, call)
     ws = torch.empty(max(256, (nbytes + 255) // 256 * 256), dtype=torch.uint8, device=device)

@@ -60,3 +60,21 @@ def test_noalloc_gives_the_workspace_bits_call_after_call():
         assert np.array_equal(o_n, o_w) and np.array_equal(l_n, l_w), f"call {i}: noalloc bits differ"
         ref_o, ref_l = gc.run_oracle(w, layer, step, gc.host(bufs), workloads.to_numpy(q), lw)
         gc.assert_attn_close(o_n, l_n, ref_o, ref_l, f"noalloc call {i}")
+
+
+# a small call, then one with more (cell, KV head) pairs, whose counters would
+# lie where the small call's partial results are if the counter block moved
+# with the shape: bf16, and f32 on the shared-prompt route
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_more_pairs_after_fewer(dtype):
+    few = workloads.get("qwen3-4b").with_(n_layers=4, n_q_heads=32, n_kv_heads=8, head_dim=128, prompt_len=900,
+                                          span=(33, 850), n_steps=20, donor=DONOR_BLANK, dtype=dtype, scale=128 ** -0.5,
+                                          cells=tuple((i % 5, i % 3) for i in range(8)))
+    many = few.with_(cells=tuple((i % 5, i % 3) for i in range(40)))
+    for i, w in enumerate((few, many, few, many)):
+        lw = workloads.cell_lw(w)
+        gc.announce(f"noalloc pairs {i}: {dtype} {w.n_cells * w.n_kv_heads} pairs")
+        bufs = gc.gpu_layer(w, 2)
+        q = workloads.make_q(w, 2, 9, device="cuda")
+        (o_n, l_n), (o_w, l_w) = _pair(w, 2, 9, bufs, q, lw)
+        assert np.array_equal(o_n, o_w) and np.array_equal(l_n, l_w), f"call {i}: noalloc bits differ"
