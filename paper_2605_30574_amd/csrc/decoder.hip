@@ -370,16 +370,23 @@ int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int32_t
 // of 32 rows and 64 columns fill the GPU (us, library against this, 128 rows:
 // K = 4096, 4096 columns 39.2 / 22.6, 2560 columns 40.9 / 23.2, K = 12288, 4096
 // columns 106.5 / 59.5; a barrier every 32 of K instead of every 128: 27.2,
-// 26.5, 70.0).  Other numbers of rows have library tiles that fit (112 rows:
-// 23.3) or sums in another order (96 rows, 2560 columns), fewer columns are
-// split over K there, and more than one round of tiles loses (K = 4096, 12288
-// columns: 42.6 / 68.4).
+// 26.5, 70.0).  The rule names 64 and 128 rows because at just these the
+// library takes slower kernels than beside them (K = 12288, 4096 columns,
+// library / this: 63 rows 42 / 56 and other bits, 64 rows 65 / 57, 65 rows
+// 50 / 57, 127 rows 49 / 57, 128 rows 82 / 58).  More than one round of tiles
+// loses (K = 4096, 12288 columns: 42.6 / 68.4).  Where the library splits K the
+// sums differ and its time is as good: 2048 columns at 128 rows (K = 8192:
+// 34 / 39), and every width from K = 17920 on (K = 18944, 64 rows, 3072
+// columns: 74 / 86).  Up to K = 16384 and at the other widths the bits were the
+// same at all of 1500 random sizes.
 using Product = Head<2, 1, 5, 4, 1, 4, true>;
-constexpr int kProductCols = 2048;   // fewer: left to the library
+constexpr int kProductCols = 2048;     // fewer: left to the library
+constexpr int kProductMaxK = 16384;
 
 int32_t splice_decoder_product_takes(int32_t rows, int32_t k, int32_t n) {
-    return (rows == 64 || rows == 128) && k >= 128 && k % 128 == 0 && k <= 1 << 20 && n >= kProductCols && n % 8 == 0 &&
-           n <= 1 << 24 && (int64_t)(rows / 32) * ((n + Product::COLS - 1) / Product::COLS) <= compute_units();
+    return (rows == 64 || rows == 128) && k >= 128 && k % 128 == 0 && k <= kProductMaxK && n >= kProductCols &&
+           !(rows == 128 && n == kProductCols) && n % 8 == 0 &&
+           (int64_t)(rows / 32) * ((n + Product::COLS - 1) / Product::COLS) <= compute_units();
 }
 
 int32_t splice_decoder_product(const void *x, const void *w, void *y, int32_t rows, int32_t k, int32_t n, void *stream) {

@@ -72,7 +72,10 @@ def _compare(make, wt, tokens, steps, what, pos=None):
     (1, 32, 32, 8, 2, 1, 64, 1), (16, 96, 160, 136, 4, 2, 64, 2), (17, 256, 416, 1000, 8, 2, 64, 1),
     (33, 320, 96, 264, 4, 4, 128, 2), (65, 128, 512, 520, 4, 2, 256, 1), (128, 512, 768, 4104, 8, 8, 64, 1),
     (129, 224, 352, 264, 4, 2, 64, 1), (256, 256, 64, 512, 2, 1, 64, 1), (24, 1056, 64, 66600, 2, 1, 64, 1),
-    (100, 1056, 64, 66600, 2, 1, 64, 1), (64, 2048, 256, 264, 32, 4, 64, 1), (128, 2056, 2176, 264, 16, 2, 128, 2), (9, 72, 104, 100, 4, 2, 64, 1)])
+    (100, 1056, 64, 66600, 2, 1, 64, 1), (64, 2048, 256, 264, 32, 4, 64, 1), (128, 2056, 2176, 264, 16, 2, 128, 2), (9, 72, 104, 100, 4, 2, 64, 1),
+    # the second layer's cache rows follow the first one's products: the query, output and down projections the
+    # library's own kernel takes, and the 2048 columns at 128 rows it leaves
+    (64, 2048, 2176, 264, 32, 4, 64, 2), (128, 2560, 2176, 264, 32, 8, 128, 2), (128, 2048, 2176, 264, 32, 4, 64, 2)])
 def test_fused_pass_keeps_the_bits(C, d, F, V, Hq, Hkv, D, N):
     make, wt, tokens, steps = _decoder(C, d, F, V, Hq, Hkv, D, N)
     _compare(make, wt, tokens, steps, f"C={C} d={d} F={F} V={V} D={D}")
@@ -181,6 +184,29 @@ def test_product(rows, K, N):
     bound = 2.0 ** -8 * want.abs() + K * 2.0 ** -24 * (x.double().abs() @ w.double().abs())   # rounding, fp32 sums
     assert ((y[:rows].double() - want).abs() <= bound).all() and (y[rows] == 7).all()
     assert lib.splice_decoder_product(xp.data_ptr(), w.data_ptr(), y.data_ptr(), rows, K + 32, N, None) == sp.SPLICE_EUNSUPPORTED
+
+
+# the sizes of the models' projections, the smallest and largest K, columns that
+# fill the last tile in part: where a pass takes the own product, its bits are
+# those of the operation it replaces
+@pytest.mark.parametrize("rows", [64, 128])
+@pytest.mark.parametrize("K", [128, 1408, 2048, 2560, 4096, 8192, 9728, 12288, 14336, 16384])
+def test_product_has_the_operations_bits(rows, K):
+    g = torch.Generator(device="cuda").manual_seed(K + rows)
+    lib = decode._library()
+    x = torch.randn(rows, K, generator=g, device="cuda").bfloat16()
+    xp = x.view(rows // 16, 16, K // 32, 32).permute(2, 0, 1, 3).contiguous()
+    for N in (2048, 2056, 2560, 3080, 4000, 4096, 5120, 8192):
+        takes = lib.splice_decoder_product_takes(rows, K, N) == 1
+        assert takes == (N <= 4096 and N > 2048 if rows == 128 else True)
+        if not takes:
+            continue
+        w = (torch.randn(K, N, generator=g, device="cuda") * K ** -0.5).bfloat16()
+        y = torch.empty(rows, N, device="cuda", dtype=torch.bfloat16)
+        gc.announce(f"product bits {rows}x{K}x{N}")
+        assert lib.splice_decoder_product(xp.data_ptr(), w.data_ptr(), y.data_ptr(), rows, K, N, None) == 0
+        assert torch.equal(y.view(torch.int16), (x @ w).view(torch.int16)), N
+    assert lib.splice_decoder_product_takes(rows, 17920, 4096) == 0   # the library splits K there
 
 
 @pytest.mark.parametrize("rows,vocab", [(1, 1), (3, 257), (130, 1023), (7, 70001)])
