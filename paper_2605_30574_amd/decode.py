@@ -29,6 +29,8 @@ from typing import List, Optional
 
 import numpy as np
 import torch
+from torch.autograd import forward_ad
+from torch.utils._device import DeviceContext
 
 from . import splice as S
 
@@ -58,6 +60,15 @@ def _library():
     return lib
 
 
+def _unwatched() -> bool:
+    """Whether nothing follows the operations of a pass but autograd's backward graph (see _plain): no function
+    transform (vmap, jvp, ...), no forward-mode level, no tracer and no mode that sees each operation."""
+    return not (torch._C._are_functorch_transforms_active() or forward_ad._current_level >= 0 or
+                torch._C._len_torch_dispatch_stack() > 0 or torch._C._get_tracing_state() is not None or
+                torch.compiler.is_compiling() or
+                any(type(m) is not DeviceContext for m in torch.overrides._get_current_function_mode_stack()))
+
+
 def _plain(t, device, *shape) -> bool:
     """A bf16 matrix of this shape on the device that autograd does not follow (any strides)."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == torch.bfloat16 and t.device == device and
@@ -70,7 +81,7 @@ def _dense(t) -> bool:
 
 def greedy(logits: torch.Tensor) -> torch.Tensor:
     """The lowest index of the largest logit of every row (int64)."""
-    if not (type(logits) is torch.Tensor and logits.is_cuda and logits.dim() == 2 and logits.is_contiguous() and
+    if not (type(logits) is torch.Tensor and _unwatched() and logits.is_cuda and logits.dim() == 2 and logits.is_contiguous() and
             logits.dtype == torch.float32 and 0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
         return torch.argmax(logits, dim=-1)
     n, vocab = logits.shape
@@ -156,7 +167,7 @@ class SweepDecoder:
         """Whether the library's kernels take this pass (x: the embedded tokens)."""
         w, wt = self.w, self.wt
         C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
-        if not (x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
+        if not (_unwatched() and x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
                 (pos is None or (pos.is_cuda and tuple(pos.shape) == (C,)))):
             return False
         for p in wt["layers"]:

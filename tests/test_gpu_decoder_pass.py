@@ -11,6 +11,7 @@ and |w| about d^-1/2, so that sum is below 8 sqrt(d)."""
 import numpy as np
 import pytest
 import torch
+from torch.autograd import forward_ad
 
 import gpu_common as gc
 import paper_2605_30574_amd as sp
@@ -115,6 +116,35 @@ def test_other_weights_take_the_written_out_pass():
         assert dec._fused(x, None)
     wt["layers"][0]["norm_1"] = keep
     assert not dec._fused(x.float(), None) and not dec._fused(x, torch.arange(5))
+
+
+def test_transforms_and_forward_mode_see_the_head():
+    """A dual or transformed head's product is the operation, which carries the tangent (and the batch)."""
+    make, wt, tokens, steps = _decoder(6, 96, 160, 136, 4, 2, 64, 1)
+    head, tan = wt["lm_head"], torch.randn_like(wt["lm_head"])
+    fused = make(True)
+
+    def logits(w):
+        wt["lm_head"] = w
+        try:
+            return fused.forward(tokens, steps)
+        finally:
+            wt["lm_head"] = head
+
+    gc.announce("decoder pass under vmap and forward mode")
+    with torch.no_grad():
+        dec = make(False)
+        want = dec.forward(tokens, steps)
+        wt["lm_head"] = tan
+        want_tan = make(False).forward(tokens, steps)   # the logits are linear in the head
+        wt["lm_head"] = head
+    with forward_ad.dual_level():
+        got = forward_ad.unpack_dual(logits(forward_ad.make_dual(head, tan)))
+        assert torch.equal(got.primal, want) and torch.equal(got.tangent, want_tan)
+    both = torch.vmap(lambda w: logits(w))(torch.stack([head, tan]))
+    assert torch.allclose(both, torch.stack([want, want_tan]), rtol=2 ** -7, atol=1e-3)
+    toks = torch.vmap(decode.greedy)(torch.stack([want, want_tan]))
+    assert torch.equal(toks, torch.argmax(torch.stack([want, want_tan]), -1))
 
 
 def test_norm_rounds_as_the_operations():
