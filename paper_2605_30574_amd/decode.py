@@ -168,7 +168,7 @@ class SweepDecoder:
         w, wt = self.w, self.wt
         C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
         if not (_unwatched() and x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
-                (pos is None or (pos.is_cuda and tuple(pos.shape) == (C,)))):
+                (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
             return False
         for p in wt["layers"]:
             F = p["w_gate"].shape[-1]

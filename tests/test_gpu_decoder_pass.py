@@ -8,6 +8,8 @@ summed in fp32 in another order, then rounded to bf16 as the operation's
 output is, so a logit differs by at most one bf16 step (2^-7 of its size) plus
 both sums' own error, d 2^-24 times the sum of |h w| at most.  |h| is about 1
 and |w| about d^-1/2, so that sum is below 8 sqrt(d)."""
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -116,6 +118,8 @@ def test_other_weights_take_the_written_out_pass():
         assert dec._fused(x, None)
     wt["layers"][0]["norm_1"] = keep
     assert not dec._fused(x.float(), None) and not dec._fused(x, torch.arange(5))
+    elsewhere = types.SimpleNamespace(is_cuda=True, shape=(5,), device=torch.device("cuda", x.device.index + 1))
+    assert not dec._fused(x, elsewhere)   # the operation refuses positions on another GPU
 
 
 def test_transforms_and_forward_mode_see_the_head():
