@@ -167,6 +167,8 @@ class SweepDecoder:
         """Whether the library's kernels take this pass (x: the embedded tokens)."""
         w, wt = self.w, self.wt
         C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
+        if torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") != torch.bfloat16:
+            return False   # the products are another type's
         if not (_unwatched() and x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
                 (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
             return False

@@ -151,6 +151,19 @@ def test_transforms_and_forward_mode_see_the_head():
     assert torch.equal(toks, torch.argmax(torch.stack([want, want_tan]), -1))
 
 
+def test_autocast_passes():
+    make, wt, tokens, steps = _decoder(6, 96, 160, 136, 4, 2, 64, 1)
+    for dtype in (torch.float16, torch.bfloat16):
+        with torch.autocast("cuda", dtype):
+            gc.announce(f"decoder pass under autocast {dtype}")
+            a, b = make(True), make(False)
+            assert a._fused(wt["embed"][tokens], None) == (dtype == torch.bfloat16)
+            got, want = a.forward(tokens, steps), b.forward(tokens, steps)
+        assert torch.allclose(got, want, rtol=2 ** -7, atol=1e-3)
+        for n in ("gen_k", "gen_v"):
+            assert torch.equal(a.caches[0][n], b.caches[0][n])
+
+
 def test_norm_rounds_as_the_operations():
     g = torch.Generator(device="cuda").manual_seed(3)
     C, d, lib = 256, 1024, decode._library()
