@@ -141,6 +141,8 @@ class SweepDecoder:
         C, Hq, Hkv, D = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim
         cdt = wt["embed"].dtype
         x = wt["embed"][tokens]
+        if pos is None and getattr(self.positions, "__func__", None) is not SweepDecoder.positions:
+            pos = self.positions(steps)   # not the T_p + s that the kernels compute
         if self._fused(x, pos):
             return self._forward_fused(x, steps, pos)
         x = x.float()

@@ -102,6 +102,19 @@ def test_given_positions_finished_cells_and_strided_weights():
     _compare(make, wt, tokens, steps, "strided weights")
 
 
+def test_overridden_positions_are_used():
+    make, wt, tokens, steps = _decoder(9, 96, 160, 136, 4, 2, 64, 1)
+    got = []
+    for given in (False, True):
+        dec = make(True)
+        far = dec.positions(steps) + 1000
+        if not given:
+            dec.positions = lambda s: far
+        gc.announce(f"decoder pass, positions given={given}")
+        got.append((dec.forward(tokens, steps, far if given else None), dec.caches[0]["gen_k"]))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
 def test_other_weights_take_the_written_out_pass():
     make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
     dec = make(True)
