@@ -79,10 +79,15 @@ def _dense(t) -> bool:
     return t.is_contiguous() and t.data_ptr() % 16 == 0
 
 
+def _current(device) -> bool:
+    """Whether kernels are launched on this GPU: a launch goes to the current device, an operation to its tensors'."""
+    return device.index == torch.cuda.current_device()
+
+
 def greedy(logits: torch.Tensor) -> torch.Tensor:
     """The lowest index of the largest logit of every row (int64)."""
-    if not (type(logits) is torch.Tensor and _unwatched() and logits.is_cuda and logits.dim() == 2 and logits.is_contiguous() and
-            logits.dtype == torch.float32 and 0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
+    if not (type(logits) is torch.Tensor and _unwatched() and logits.is_cuda and _current(logits.device) and
+            logits.dim() == 2 and logits.is_contiguous() and logits.dtype == torch.float32 and 0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
         return torch.argmax(logits, dim=-1)
     n, vocab = logits.shape
     tokens = torch.empty(n, dtype=torch.int64, device=logits.device)
@@ -171,7 +176,7 @@ class SweepDecoder:
         C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
         if torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") != torch.bfloat16:
             return False   # the products are another type's
-        if not (_unwatched() and x.is_cuda and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
+        if not (_unwatched() and x.is_cuda and _current(dev) and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
                 (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
             return False
         for p in wt["layers"]:

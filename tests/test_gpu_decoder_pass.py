@@ -115,6 +115,16 @@ def test_overridden_positions_are_used():
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+def test_another_current_device_keeps_the_operations(monkeypatch):
+    make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
+    x = wt["embed"][tokens]
+    assert make(True)._fused(x, None)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: x.device.index + 1)
+    assert not make(True)._fused(x, None)
+    monkeypatch.setattr(decode, "_library", None)   # greedy() would call it
+    assert decode.greedy(x.float()).shape == (5,)
+
+
 def test_other_weights_take_the_written_out_pass():
     make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
     dec = make(True)
