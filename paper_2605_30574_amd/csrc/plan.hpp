@@ -260,6 +260,9 @@ constexpr int kWideF32Items = 256;               // prompt work groups aimed for
 constexpr int kWideF32Chunk = 64;                // keys of a chunk, at least
 constexpr int kWideF32LongChunk = 256;           // ... and at most, up to kWideF32MaxChunks chunks
 constexpr int kWideF32MaxChunks = 16;
+// D = 256: the longest chunk, whose outputs are one chain of tiles there (error
+// against the general route's 0.90 at 256 keys a chunk, 1.22 at 512)
+constexpr int kWideF32MaxChunkD256 = 384;
 constexpr int64_t kWideF32MaxBytes = (int64_t)64 << 20;   // partial results, at most
 
 inline int wide_f32_chunk_target(const splice_shape &sh) {
@@ -381,7 +384,7 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
         if (p.n_p > ceil_div(geo.n_prompt, kWideF32Chunk)) p.n_p = ceil_div(geo.n_prompt, kWideF32Chunk);
         p.p_len = round_up(ceil_div(geo.n_prompt, p.n_p), 32);
         p.n_p = ceil_div(geo.n_prompt, p.p_len);
-        if (wide_f32(sh, geo.n_prompt, p.n_p)) {
+        if (wide_f32(sh, geo.n_prompt, p.n_p) && (sh.head_dim <= 128 || p.p_len <= kWideF32MaxChunkD256)) {
             p.wide = true;
             p.cellwise = false;
             p.n_g = 1;

@@ -22,8 +22,13 @@
 // 37.7 us a call, 2048 keys 113.6 -> 49; 16 cells and 1024 keys 33.6 -> 21.7.
 // The second launch costs less than counting arrivals and merging in the last
 // item to finish (1024 keys: 41 us against 56), and all partials are stored
-// plainly.  Sums are kept in short chains (eight per score, one per 16 keys for
-// the outputs): the error against 64 bits is that of the vector-ALU kernels.
+// plainly.  Sums are kept in short chains (see WideF), so that the error against
+// 64 bits is below that of the vector-ALU kernels: over 200 random shapes by D
+// and G 0.55 to 0.95 of it at D <= 128 (prompts of 200 to 40000 keys), 0.43 to
+// 0.77 at D = 256 (up to 6144).  With one chain per chunk above the 16 keys, one
+// chain over the slots in the merge and eight accumulators at D = 256 it was up
+// to 1.09 of it on average and 2.8 at prompts of 30000 keys; the short chains
+// cost 2% of a call (D = 256: 4.5%).
 //
 // Part of attn_kernels.hpp, included there after what it builds on.
 #pragma once
@@ -41,10 +46,17 @@ struct WideF {
     static constexpr int CH = ROW / 16;              // 16-byte chunks per row
     static constexpr int TILE = TK * ROW;
     static constexpr int BUF = 2 * TILE;             // K tile, then V tile
-    static constexpr int NB = D <= 128 ? 3 : 2;      // at D <= 128 three work groups a compute unit
+    static constexpr int NB = D <= 128 ? 3 : 2;      // at D <= 128 LDS for three work groups a compute unit
     static constexpr int LDS = NB * BUF;
     static constexpr int PER = TK * CH / 64 / NW;    // load instructions per wave and operand
     static constexpr int KH = TK / 16, NG = D / 16, NU = D / 64;
+    // Roundings of a chain add up, so chains are short: NS accumulators a score;
+    // for the outputs a product chain per 16 keys (D = 256: two), then chains of
+    // RAISE tiles, then those (D = 256 has no registers for these: its chunks
+    // stay short instead)
+    static constexpr int NS = D <= 128 ? 8 : 16;
+    static constexpr int NT = D <= 128 ? 1 : 2;
+    static constexpr int RAISE = D <= 128 ? 64 / TK : 0;
 };
 
 template <int D, int G>
@@ -87,9 +99,11 @@ __device__ __forceinline__ void wide_prompt_item(const AttnArgs &a, int item, ch
     list_add<X::TK>(L, ck + (size_t)post0 * X::ROW, cv + (size_t)post0 * X::ROW, k1 - post0);
     const int n_tiles = list_tiles(L);
 
-    f32x4_t o[X::NU][4];
+    f32x4_t o[X::NU][4], oh[X::RAISE ? X::NU : 1][4];   // oh, lh: the finished chains
     static_for<0, X::NU>([&](auto u) { static_for<0, 4>([&](auto j) { o[u][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }); });
-    float m = -INFINITY, lsum = 0.f;
+    if constexpr (X::RAISE)
+        static_for<0, X::NU>([&](auto u) { static_for<0, 4>([&](auto j) { oh[u][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; }); });
+    float m = -INFINITY, lsum = 0.f, lh = 0.f;
     if (n_tiles > 0) {
         // this lane's sources within a tile; chunk c of K row r sits at slot
         // c ^ (r mod 16), so that the 16 rows of a quarter-wave read touch every bank
@@ -137,11 +151,10 @@ __device__ __forceinline__ void wide_prompt_item(const AttnArgs &a, int item, ch
                     issue(ref[jn], lds0 + (uint32_t)jn * X::BUF);
                     const char *sK = lds + jj * X::BUF, *sV = sK + X::TILE;
                     const int n_valid = ref[jj].n;
-                    // eight sums of D / 8 products, added at the end: short chains, of
-                    // roundings as of dependent instructions
-                    f32x4_t s[X::KH], s8[X::KH][8];
+                    // NS sums of D / NS products, added at the end
+                    f32x4_t s[X::KH], sn[X::KH][X::NS];
                     static_for<0, X::KH>([&](auto kh) {
-                        static_for<0, 8>([&](auto j) { s8[kh][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+                        static_for<0, X::NS>([&](auto j) { sn[kh][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
                     });
                     static_for<0, X::NG>([&](auto n) {
                         static_for<0, X::KH>([&](auto kh) {
@@ -149,15 +162,16 @@ __device__ __forceinline__ void wide_prompt_item(const AttnArgs &a, int item, ch
                             const f32x4_t kf =
                                 *reinterpret_cast<const f32x4_t *>(sK + r * X::ROW + ((4 * n + quad) ^ (r & 15)) * 16);
                             static_for<0, 4>([&](auto j) {
-                                constexpr int sj = 4 * (decltype(n)::value % 2) + decltype(j)::value;
-                                s8[kh][sj] =
-                                    __builtin_amdgcn_mfma_f32_16x16x4f32(kf[(int)j], qf[n][(int)j], s8[kh][sj], 0, 0, 0);
+                                constexpr int sj = 4 * (decltype(n)::value % (X::NS / 4)) + decltype(j)::value;
+                                sn[kh][sj] =
+                                    __builtin_amdgcn_mfma_f32_16x16x4f32(kf[(int)j], qf[n][(int)j], sn[kh][sj], 0, 0, 0);
                             });
                         });
                     });
                     static_for<0, X::KH>([&](auto kh) {
-                        s[kh] = ((s8[kh][0] + s8[kh][1]) + (s8[kh][2] + s8[kh][3])) +
-                                ((s8[kh][4] + s8[kh][5]) + (s8[kh][6] + s8[kh][7]));
+                        if constexpr (X::NS == 16) static_for<0, 8>([&](auto j) { sn[kh][j] += sn[kh][j + 8]; });
+                        s[kh] = ((sn[kh][0] + sn[kh][1]) + (sn[kh][2] + sn[kh][3])) +
+                                ((sn[kh][4] + sn[kh][5]) + (sn[kh][6] + sn[kh][7]));
                     });
                     float mt = -INFINITY;
                     static_for<0, X::KH>([&](auto kh) {
@@ -174,36 +188,56 @@ __device__ __forceinline__ void wide_prompt_item(const AttnArgs &a, int item, ch
                         const float mn = need ? fmaxf(m, mt) : m;
                         const float al = need ? fast_exp2(m - (mn == -INFINITY ? 0.f : mn)) : 1.f;
                         lsum *= al;
+                        lh *= al;
                         static_for<0, X::NU>([&](auto u) { static_for<0, 4>([&](auto j) { o[u][j] *= al; }); });
+                        if constexpr (X::RAISE)
+                            static_for<0, X::NU>([&](auto u) { static_for<0, 4>([&](auto j) { oh[u][j] *= al; }); });
                         m = mn;
                     }
                     const float ms = m == -INFINITY ? 0.f : m;
-                    // per 16 keys a sum of its own, then added: chains of tiles, not of keys
                     static_for<0, X::KH>([&](auto kh) {
                         float p[4];
                         static_for<0, 4>(
                             [&](auto i) { p[(int)i] = fast_exp2(fmaf(s[kh][(int)i], a.qk_scale, -ms)); });
                         lsum += (p[0] + p[1]) + (p[2] + p[3]);
                         static_for<0, X::NU>([&](auto u) {
-                            f32x4_t t[4];
-                            static_for<0, 4>([&](auto j) { t[j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+                            f32x4_t t[X::NT][4];
+                            static_for<0, X::NT>([&](auto k) {
+                                static_for<0, 4>([&](auto j) { t[k][j] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
+                            });
                             static_for<0, 4>([&](auto i) {
                                 const f32x4_t vf = *reinterpret_cast<const f32x4_t *>(
                                     sV + (16 * kh + 4 * quad + i) * X::ROW + col * 16 + 256 * u);
+                                constexpr int k = decltype(i)::value * X::NT / 4;
                                 static_for<0, 4>([&](auto j) {
-                                    t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[(int)j], p[(int)i], t[j], 0, 0, 0);
+                                    t[k][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[(int)j], p[(int)i], t[k][j], 0, 0, 0);
                                 });
                             });
-                            static_for<0, 4>([&](auto j) { o[u][j] += t[j]; });
+                            static_for<0, 4>([&](auto j) { o[u][j] += X::NT > 1 ? t[0][j] + t[X::NT - 1][j] : t[0][j]; });
                         });
                     });
+                    if constexpr (X::RAISE) {
+                        if ((base + jj) % X::RAISE == X::RAISE - 1) {   // uniform
+                            lh += lsum;
+                            lsum = 0.f;
+                            static_for<0, X::NU>([&](auto u) {
+                                static_for<0, 4>([&](auto j) {
+                                    oh[u][j] += o[u][j];
+                                    o[u][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                                });
+                            });
+                        }
+                    }
                 }
             });
         }
         wait_vmcnt<0>();
     }
+    lsum += lh;
     lsum += __shfl_xor(lsum, 16);
     lsum += __shfl_xor(lsum, 32);
+    if constexpr (X::RAISE)
+        static_for<0, X::NU>([&](auto u) { static_for<0, 4>([&](auto j) { o[u][j] += oh[u][j]; }); });
     if (ok) {   // o[u][j][i] is d 64 u + 16 quad + 4 i + j
         using SL = Slot<D, G, false>;
         char *slot = reinterpret_cast<char *>(a.part) + pslot_off(a, cell, g, pk);
@@ -281,11 +315,15 @@ __global__ __launch_bounds__(kThreads) void wide_merge_kernel(AttnArgs a) {
     static_for<0, B>([&](auto k) {
         if (k <= a.n_p) M = fmaxf(M, mk[k]);
     });
-    float L = nz > 0 ? (float)nz * fast_exp2(-M) : 0.f;
-    f32x4_t O = {0.f, 0.f, 0.f, 0.f};
+    // four chains of slots: every addition to an output that one key dominates rounds it
+    float Lc[4] = {nz > 0 ? (float)nz * fast_exp2(-M) : 0.f, 0.f, 0.f, 0.f};
+    f32x4_t Oc[4];
+    static_for<0, 4>([&](auto c4) { Oc[c4] = f32x4_t{0.f, 0.f, 0.f, 0.f}; });
     static_for<0, B>([&](auto k) {
-        if (k <= a.n_p) fold_slot(mk[k], lk[k], ok[k], M, L, O);
+        if (k <= a.n_p) fold_slot(mk[k], lk[k], ok[k], M, Lc[k % 4], Oc[k % 4]);
     });
+    const float L = (Lc[0] + Lc[1]) + (Lc[2] + Lc[3]);
+    const f32x4_t O = (Oc[0] + Oc[1]) + (Oc[2] + Oc[3]);
     const size_t row = (size_t)c * a.Hq + hq;
     *reinterpret_cast<f32x4_t *>(a.out + row * D + d) = O * (1.f / L);
     if (d == 0) a.lse[row] = (M + log2f(L)) * kLn2;
