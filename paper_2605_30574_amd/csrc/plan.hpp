@@ -245,24 +245,38 @@ inline bool cellwise_many(const splice_shape &sh) { return sh.n_cells * sh.n_kv_
 
 // f32 calls whose cells share the reading of the prompt (wide_f32.hpp): the
 // other routes cost about what the rows' keys cost, this one a second launch
-// and the prompt items' start-up (10 to 14 us), so it takes calls with many
-// keys for each row group: G keys >= 1536 (D = 128, G = 4, 300 keys: 15.4 against
-// 15.7 us with 8 cells, 27.5 each with 64; 512 keys: 18.0 against 14.2, 34.9
-// against 31.2), at G = 8 (one work group a compute unit) above the cellwise
-// route's limit; and at least half a 64-row group (G = 4, 8 cells, 1024 keys:
-// 22.0 against 18.2).  At G <= 2 the vector ALUs do well until a compute unit
-// holds several (cell, KV head) pairs (D = 128, G = 1, 1500 keys, 128 pairs:
-// 17.3 against 19.7; D = 64, 256 pairs: 16.8 against 15.3).
+// and the prompt items' start-up (10 to 14 us).  The lines, with the time of
+// the other routes and of this one (us):
+//   * G keys >= 1536 (D = 128, G = 4, 300 keys: 15.4 / 15.7 with 8 cells, 27.5
+//     both with 64);
+//   * against the cellwise route (up to kCellwiseMaxPrompt keys) more (cell, KV
+//     head) pairs than compute units (G = 4, some 450 keys: D = 128, 94 pairs
+//     18.8 / 20.0, 200 19.5 / 21.5, 276 38.8 / 24.4; D = 64, 104 pairs 16.4 /
+//     18.7, 268 22 / 17.7; D = 256, 204 pairs 27.0 / 29.9, 312 47 / 32), and
+//     never at G = 8 (one work group a compute unit);
+//   * half a 64-row group or more a KV head (G = 4, 8 cells, 1024 keys: 22.0 /
+//     18.2);
+//   * at G >= 4, rows enough over all KV heads, 320 or at D = 64 192: the prompt
+//     is at most kWideF32MaxChunks chunks a KV head, each a chain of its tiles,
+//     so few rows leave most of the GPU idle, where the vector-ALU items spread
+//     over 512 work groups (D = 128, 32 rows of 8349 keys 29.8 / 58.3, 116 of
+//     1638 18.2 / 24.4, 288 of 711 19.7 / 20.2, 336 of 4544 49.0 / 38.9; D = 256,
+//     196 of 3146 45.0 / 52.1; D = 64, 136 of 1239 19.0 / 19.8, 232 of 5749 41.4 /
+//     31.0).  Up to 1024 keys the chains are short, and at G = 8, whose
+//     vector-ALU items cost 23 us at least, that is enough (D = 128, 48 rows of
+//     605 keys 23.2 / 18.2, 72 of 2988 25.7 / 29.9);
+//   * at G <= 2, where the vector ALUs do well until a compute unit holds
+//     several pairs, as many pairs as compute units (D = 128, G = 1, 1500 keys,
+//     128 pairs: 17.3 / 19.7; D = 64, 256 pairs: 16.8 / 15.3).
 constexpr int kWideF32Rows = 32;
+constexpr int kWideF32TotalRows = 320, kWideF32TotalRowsD64 = 192;
+constexpr int kWideF32ShortKeys = 1024;
 constexpr int kWideF32Keys = 1536;
 constexpr int kWideF32Pairs = 256;
 constexpr int kWideF32Items = 256;               // prompt work groups aimed for: one a compute unit
 constexpr int kWideF32Chunk = 64;                // keys of a chunk, at least
 constexpr int kWideF32LongChunk = 256;           // ... and at most, up to kWideF32MaxChunks chunks
 constexpr int kWideF32MaxChunks = 16;
-// D = 256: the longest chunk, whose outputs are one chain of tiles there (error
-// against the general route's 0.90 at 256 keys a chunk, 1.22 at 512)
-constexpr int kWideF32MaxChunkD256 = 384;
 constexpr int64_t kWideF32MaxBytes = (int64_t)64 << 20;   // partial results, at most
 
 inline int wide_f32_chunk_target(const splice_shape &sh) {
@@ -272,10 +286,16 @@ inline int wide_f32_chunk_target(const splice_shape &sh) {
 }
 
 inline bool wide_f32(const splice_shape &sh, int n_prompt, int n_p) {
+    if (bf16_path(sh)) return false;
     const int G = group_of(sh);
-    return !bf16_path(sh) && sh.n_cells * G >= kWideF32Rows && (int64_t)n_prompt * G >= kWideF32Keys &&
-           (G < 8 || n_prompt > kCellwiseMaxPrompt) && (G > 2 || sh.n_cells * sh.n_kv_heads >= kWideF32Pairs) &&
-           (int64_t)sh.n_cells * sh.n_kv_heads * (n_p + 1) * slot_floats(G, sh.head_dim) * 4 <= kWideF32MaxBytes;
+    const int64_t pairs = (int64_t)sh.n_cells * sh.n_kv_heads;
+    if (sh.n_cells * G < kWideF32Rows || (int64_t)n_prompt * G < kWideF32Keys) return false;
+    if (n_prompt <= kCellwiseMaxPrompt && (G >= 8 || pairs <= kWideF32Pairs)) return false;
+    if (G <= 2 ? pairs < kWideF32Pairs
+               : pairs * G < (sh.head_dim <= 64 ? kWideF32TotalRowsD64 : kWideF32TotalRows) &&
+                     !(G >= 8 && n_prompt <= kWideF32ShortKeys))
+        return false;
+    return pairs * (n_p + 1) * slot_floats(G, sh.head_dim) * 4 <= kWideF32MaxBytes;
 }
 
 struct AttnPlan {
@@ -384,7 +404,7 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
         if (p.n_p > ceil_div(geo.n_prompt, kWideF32Chunk)) p.n_p = ceil_div(geo.n_prompt, kWideF32Chunk);
         p.p_len = round_up(ceil_div(geo.n_prompt, p.n_p), 32);
         p.n_p = ceil_div(geo.n_prompt, p.p_len);
-        if (wide_f32(sh, geo.n_prompt, p.n_p) && (sh.head_dim <= 128 || p.p_len <= kWideF32MaxChunkD256)) {
+        if (wide_f32(sh, geo.n_prompt, p.n_p)) {
             p.wide = true;
             p.cellwise = false;
             p.n_g = 1;

@@ -25,7 +25,8 @@
 // plainly.  Sums are kept in short chains (see WideF), so that the error against
 // 64 bits is below that of the vector-ALU kernels: over 200 random shapes by D
 // and G 0.55 to 0.95 of it at D <= 128 (prompts of 200 to 40000 keys), 0.43 to
-// 0.77 at D = 256 (up to 6144).  With one chain per chunk above the 16 keys, one
+// 0.77 at D = 256 (0.15 to 0.51 from 6144 keys on, where theirs are longer
+// still).  With one chain per chunk above the 16 keys, one
 // chain over the slots in the merge and eight accumulators at D = 256 it was up
 // to 1.09 of it on average and 2.8 at prompts of 30000 keys; the short chains
 // cost 2% of a call (D = 256: 4.5%).
@@ -52,8 +53,7 @@ struct WideF {
     static constexpr int KH = TK / 16, NG = D / 16, NU = D / 64;
     // Roundings of a chain add up, so chains are short: NS accumulators a score;
     // for the outputs a product chain per 16 keys (D = 256: two), then chains of
-    // RAISE tiles, then those (D = 256 has no registers for these: its chunks
-    // stay short instead)
+    // RAISE tiles, then those (D = 256 has no registers for these)
     static constexpr int NS = D <= 128 ? 8 : 16;
     static constexpr int NT = D <= 128 ? 1 : 2;
     static constexpr int RAISE = D <= 128 ? 64 / TK : 0;

@@ -44,6 +44,13 @@ CASES = {
     "d256-g2": (33, 16, 8, 256, 769, (64, 700), DONOR_DIFF),
     "d256-g4": (8, 4, 1, 256, 400, (7, 391), DONOR_BLANK),
     "d64-g1": (64, 4, 4, 64, 1537, (1, 1536), DONOR_BLANK),
+    # the same edges with rows enough for the route (192 over all KV heads at D = 64, else 320)
+    "d128-g4-ragged-rows": (41, 8, 2, 128, 1031, (33, 999), DONOR_DIFF),
+    "d128-g4-zero-rows": (80, 8, 2, 128, 777, (16, 776), DONOR_ZERO),
+    "d128-g4-window-rows": (47, 8, 2, 128, 900, (100, 800), DONOR_BLANK, 500),
+    "d64-g8-rows": (25, 16, 2, 64, 530, (3, 529), DONOR_BLANK),
+    "d256-g4-rows": (81, 4, 1, 256, 400, (7, 391), DONOR_BLANK),
+    "d64-g1-rows": (80, 4, 4, 64, 1537, (1, 1536), DONOR_BLANK),
 }
 
 
@@ -81,10 +88,11 @@ def test_shared_prompt_route(name):
         assert np.abs(o4 - ref_o).max() <= ABS
 
 
-def test_donor_equal_clean_is_unspliced_up_to_grouping():
+@pytest.mark.parametrize("C", [16, 40])   # the general route, the shared-prompt one
+def test_donor_equal_clean_is_unspliced_up_to_grouping(C):
     """Spliced and unspliced cells sit in different row groups, which share no
     arithmetic: the bits of a cell depend on neither."""
-    w = _w(16, 8, 2, 128, 700, (40, 650), DONOR_BLANK)
+    w = _w(C, 8, 2, 128, 700, (40, 650), DONOR_BLANK)
     lw = workloads.cell_lw(w)
     never = np.array([[w.n_layers, 0]] * w.n_cells, dtype=np.int32)
     bufs = gc.gpu_layer(w, 2)

@@ -26,6 +26,10 @@ int noalloc_ranges(const splice_shape *sh, const splice_call *call, int64_t *r) 
     r[2] = w.part_off; r[3] = r[2] + w.part_bytes; r[4] = kNoallocBytes;
     return 1;
 }
+// f32: 1 where the call takes the shared-prompt route
+int takes_wide(const splice_shape *sh, const splice_call *call) {
+    return plan_from_geo(*sh, *call, geometry(*sh, *call), sh->n_cells / 2, sh->n_cells).wide;
+}
 }
 """
 
@@ -58,3 +62,15 @@ def test_no_call_leaves_partials_where_another_keeps_counters(plan):
     last_counter, first_part = max(r[1] for r in ranges), min(r[2] for r in ranges)
     assert last_counter <= first_part, (last_counter, first_part)
     assert all(S.SPLICE_NOALLOC_WORKSPACE_BYTES < r[4] and r[3] <= r[4] for r in ranges)
+
+
+# (cells, KV heads, G, D, prompt keys): measured on both routes, see wide_f32 in plan.hpp
+@pytest.mark.parametrize("dims,wide", [
+    ((8, 1, 4, 128, 8349), False), ((29, 1, 4, 128, 1638), False), ((9, 1, 4, 64, 3964), False),
+    ((9, 4, 4, 256, 1528), False), ((49, 1, 4, 256, 3146), False), ((9, 1, 8, 128, 2988), False),
+    ((27, 8, 4, 64, 422), False), ((50, 4, 4, 128, 435), False), ((51, 4, 4, 256, 417), False),
+    ((69, 4, 4, 128, 446), True), ((67, 4, 4, 64, 450), True), ((84, 1, 4, 128, 4544), True), ((25, 4, 4, 64, 2917), True), ((39, 4, 4, 256, 651), True),
+    ((17, 2, 4, 64, 1239), False), ((29, 1, 8, 64, 5749), True), ((6, 1, 8, 128, 605), True), ((79, 4, 1, 128, 1813), True),
+    ((59, 1, 8, 128, 3821), True), ((64, 8, 4, 128, 1024), True), ((46, 8, 1, 128, 4360), True)])
+def test_f32_route_needs_rows_for_the_whole_gpu(plan, dims, wide):
+    assert plan.takes_wide(ctypes.byref(_shape(*dims, dtype="f32")), ctypes.byref(sp.make_call(0, 5, 0, 1.0))) == wide
