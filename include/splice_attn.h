@@ -199,16 +199,19 @@ SPLICE_API int32_t splice_decode_attn(const splice_shape *shape, const splice_ca
  * serving loops that must not allocate, harnesses that forbid it).  The
  * split-K partials and arrival counters live in a library-owned device
  * array, one per GPU, held until the process ends, in place of a workspace of
- * SPLICE_NOALLOC_WORKSPACE_BYTES bytes; calls whose splice_decode_attn_workspace_bytes(shape,
- * call) exceeds it return SPLICE_EWORKSPACE before any device work.  The
+ * SPLICE_NOALLOC_WORKSPACE_BYTES bytes; a call that needs more returns
+ * SPLICE_EWORKSPACE before any device work (never one whose
+ * splice_decode_attn_workspace_bytes(shape, call) is within it; a bf16 call
+ * may need less than those bytes, which also hold a forked sweep's).  The
  * first call on a device takes the array's address and clears it with a
  * fill kernel on `stream` (make that first call outside graph capture);
  * every later call, of whatever shape, finds the arrival counters at zero:
  * each call re-arms the counters it uses, and the counters have a block of
- * their own that no call's partial results reach.  All calls on one GPU share the array:
- * calls that overlap on one GPU (other streams, other threads) race and must
- * be ordered by the caller, e.g. on one stream.  Arguments, results, errors
- * and bits are those of splice_decode_attn (same kernels, same plan).
+ * their own that no call's partial results reach.  All calls on one GPU
+ * share the array: calls that overlap on one GPU (other streams, other
+ * threads) race and must be ordered by the caller, e.g. on one stream.
+ * Arguments, results, errors and bits are those of splice_decode_attn (same
+ * kernels, same plan: how a call is cut does not depend on its workspace).
  */
 #define SPLICE_NOALLOC_WORKSPACE_BYTES ((size_t)32 << 20)
 SPLICE_API int32_t splice_decode_attn_noalloc(const splice_shape *shape, const splice_call *call,

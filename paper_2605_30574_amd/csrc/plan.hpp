@@ -277,12 +277,21 @@ constexpr int kWideF32Items = 256;               // prompt work groups aimed for
 constexpr int kWideF32Chunk = 64;                // keys of a chunk, at least
 constexpr int kWideF32LongChunk = 256;           // ... and at most, up to kWideF32MaxChunks chunks
 constexpr int kWideF32MaxChunks = 16;
-constexpr int64_t kWideF32MaxBytes = (int64_t)64 << 20;   // partial results, at most
-
 inline int wide_f32_chunk_target(const splice_shape &sh) {
     const int groups = sh.n_kv_heads * (ceil_div((int64_t)sh.n_cells * group_of(sh), group_rows(sh.head_dim)) + 1);
     const int t = kWideF32Items / groups;
     return t < 1 ? 1 : (t > kWideF32MaxChunks ? kWideF32MaxChunks : t);
+}
+
+// The most chunks whose partial results fit the no-allocation entry's array, so
+// that it and splice_decode_attn take one plan; calls with that many pairs
+// fill the GPU with a few chunks.
+inline int wide_f32_chunk_cap(const splice_shape &sh) {
+    const int64_t pairs = (int64_t)sh.n_cells * sh.n_kv_heads;
+    const int64_t slot = (int64_t)slot_floats(group_of(sh), sh.head_dim) * 4;
+    const int64_t room = (int64_t)SPLICE_NOALLOC_WORKSPACE_BYTES - 512 - 4 * pairs;   // statistics, counters
+    const int64_t cap = pairs > 0 && room > 0 ? room / (pairs * slot) - 1 : 0;
+    return cap < 0 ? 0 : (cap < kWideF32MaxChunks ? (int)cap : kWideF32MaxChunks);
 }
 
 inline bool wide_f32(const splice_shape &sh, int n_prompt, int n_p) {
@@ -295,7 +304,7 @@ inline bool wide_f32(const splice_shape &sh, int n_prompt, int n_p) {
                : pairs * G < (sh.head_dim <= 64 ? kWideF32TotalRowsD64 : kWideF32TotalRows) &&
                      !(G >= 8 && n_prompt <= kWideF32ShortKeys))
         return false;
-    return pairs * (n_p + 1) * slot_floats(G, sh.head_dim) * 4 <= kWideF32MaxBytes;
+    return n_p >= 1;
 }
 
 struct AttnPlan {
@@ -398,18 +407,22 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
     p.geo = geo;
     p.wide = false;
     if (wide_ok && !bf16_path(sh) && call.split_keys == 0 && geo.n_prompt > 0) {
+        const int cap = wide_f32_chunk_cap(sh);
         p.n_p = wide_f32_chunk_target(sh);
         const int least = ceil_div(geo.n_prompt, kWideF32LongChunk);   // short chains of sums
-        if (p.n_p < least) p.n_p = least < kWideF32MaxChunks ? least : kWideF32MaxChunks;
-        if (p.n_p > ceil_div(geo.n_prompt, kWideF32Chunk)) p.n_p = ceil_div(geo.n_prompt, kWideF32Chunk);
-        p.p_len = round_up(ceil_div(geo.n_prompt, p.n_p), 32);
-        p.n_p = ceil_div(geo.n_prompt, p.p_len);
+        if (p.n_p < least) p.n_p = least;
+        if (p.n_p > cap) p.n_p = cap;
         if (wide_f32(sh, geo.n_prompt, p.n_p)) {
+            if (p.n_p > ceil_div(geo.n_prompt, kWideF32Chunk)) p.n_p = ceil_div(geo.n_prompt, kWideF32Chunk);
+            p.p_len = round_up(ceil_div(geo.n_prompt, p.n_p), 32);
+            p.n_p = ceil_div(geo.n_prompt, p.p_len);
             p.wide = true;
             p.cellwise = false;
             p.n_g = 1;
             p.g_len = geo.n_gen;
-            p.n_slots = p.n_p + 1;
+            // a call asks for no less than it would without this route
+            const int general = plan_from_geo(sh, call, geo, n_clean, n_active, res, same_rows, false).n_slots;
+            p.n_slots = p.n_p + 1 > general ? p.n_p + 1 : general;
             p.n_prompt_items = kXcds * row_groups(sh, n_clean, n_active) * ceil_div((int64_t)sh.n_kv_heads * p.n_p, kXcds);
             p.n_gen_items = sh.n_cells * sh.n_kv_heads;
             p.gen_pairs = 1;
@@ -590,8 +603,14 @@ inline int worst_default_slots(const splice_shape &sh) {
                                           bf16_path(sh) ? kWideMinChunk : kMinChunk);
     if (bf16_path(sh)) return prompt + 1;
     const int items = prompt + max_default_chunks(sh.gen_capacity, gen_chunk_target(sh));
-    const int wide = max_default_chunks(sh.prompt_len, kWideF32MaxChunks, kWideF32Chunk) + 1;
-    return items > wide || !wide_f32(sh, sh.prompt_len, 1) ? items : wide;
+    // a window may leave fewer keys: the shared-prompt rule holds at some number
+    // of keys up to prompt_len if at that, or at the most "short" ones
+    const int cap = wide_f32_chunk_cap(sh);
+    const int few = sh.prompt_len < kWideF32ShortKeys ? sh.prompt_len : kWideF32ShortKeys;
+    const int wide = wide_f32(sh, sh.prompt_len, cap) || wide_f32(sh, few, cap)
+                         ? max_default_chunks(sh.prompt_len, cap, kWideF32Chunk) + 1
+                         : 0;
+    return items > wide ? items : wide;
 }
 
 }  // namespace splice

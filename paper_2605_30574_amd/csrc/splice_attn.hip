@@ -170,9 +170,7 @@ splice::Residency residency(const void *kernel, int threads) {
 // a forked sweep plans over its diverged cells only, and by default fewer
 // computed cells take more prompt chunks (with an explicit split_keys the
 // chunks do not depend on them); without it, a call that computes every cell.
-// An f32 call that takes the shared-prompt route when it has the space for its
-// slots can do with less (least).
-int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call, bool every_count, bool least = false) {
+int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call, bool every_count) {
     int32_t rc = splice::validate_shape(shape);
     if (rc != SPLICE_OK) return rc;
     int n_slots;
@@ -184,10 +182,8 @@ int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call,
         const int n_lo = every_count && call->split_keys == 0 ? 1 : n_hi;
         n_slots = 0;
         for (int n = n_lo; n <= n_hi; ++n) {   // the slots do not depend on the cell split
-            const int k = splice::plan_from_geo(*shape, *call, geo, 0, n, splice::Residency(), true, false).n_slots;
-            const int wide = least ? 0 : splice::plan_from_geo(*shape, *call, geo, 0, n).n_slots;
+            const int k = splice::plan_from_geo(*shape, *call, geo, 0, n).n_slots;
             n_slots = k > n_slots ? k : n_slots;
-            n_slots = wide > n_slots ? wide : n_slots;
         }
         if (n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
     } else {
@@ -390,10 +386,8 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
 
     const splice::Residency res =
         splice::bf16_path(sh) ? residency((const void *)kern.items, threads) : splice::Residency();
-    splice::AttnPlan plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, g_lo.n_gen == g_hi.n_gen);
-    if (plan.wide && (noalloc ? (size_t)SPLICE_NOALLOC_WORKSPACE_BYTES : workspace_bytes) <
-                         splice::workspace_layout(sh, plan.n_slots).total)   // the route with fewer slots
-        plan = splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, true, false);
+    const splice::AttnPlan plan =
+        splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, g_lo.n_gen == g_hi.n_gen);
     if (plan.n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
     const splice::WorkspaceLayout wl =
         noalloc ? splice::noalloc_layout(sh, plan.n_slots) : splice::workspace_layout(sh, plan.n_slots);
@@ -555,7 +549,7 @@ int32_t splice_decode_attn_noalloc(const splice_shape *shape, const splice_call 
                                    void *stream) {
     // validation and the size check come first: a call that does not fit is
     // rejected before any device work
-    const int64_t need = attn_workspace_bytes(shape, call, false, true);   // every cell is computed
+    const int64_t need = attn_workspace_bytes(shape, call, false);   // every cell is computed
     if (need < 0) return (int32_t)need;
     if (need > (int64_t)SPLICE_NOALLOC_WORKSPACE_BYTES) return SPLICE_EWORKSPACE;
     void *ws = nullptr;

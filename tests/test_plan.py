@@ -30,6 +30,14 @@ int noalloc_ranges(const splice_shape *sh, const splice_call *call, int64_t *r) 
 int takes_wide(const splice_shape *sh, const splice_call *call) {
     return plan_from_geo(*sh, *call, geometry(*sh, *call), sh->n_cells / 2, sh->n_cells).wide;
 }
+// workspace bytes of the call's plan [0] and of the plan without that route [1], chunks [2] and their length [3]
+void plan_bytes(const splice_shape *sh, const splice_call *call, int64_t *r) {
+    const Geometry geo = geometry(*sh, *call);
+    const AttnPlan p = plan_from_geo(*sh, *call, geo, 0, sh->n_cells);
+    const AttnPlan q = plan_from_geo(*sh, *call, geo, 0, sh->n_cells, Residency(), true, false);
+    r[0] = workspace_layout(*sh, p.n_slots).total; r[1] = workspace_layout(*sh, q.n_slots).total;
+    r[2] = p.n_p; r[3] = p.p_len;
+}
 }
 """
 
@@ -74,3 +82,23 @@ def test_no_call_leaves_partials_where_another_keeps_counters(plan):
     ((59, 1, 8, 128, 3821), True), ((64, 8, 4, 128, 1024), True), ((46, 8, 1, 128, 4360), True)])
 def test_f32_route_needs_rows_for_the_whole_gpu(plan, dims, wide):
     assert plan.takes_wide(ctypes.byref(_shape(*dims, dtype="f32")), ctypes.byref(sp.make_call(0, 5, 0, 1.0))) == wide
+
+
+def test_both_entries_take_one_f32_plan(plan):
+    """The shared-prompt route never asks for more than the no-allocation array
+    holds, nor for other bytes than the query says, so no call's route (and so
+    no call's bits) depends on its workspace, and what that entry accepts is
+    what it accepted without the route."""
+    wide, limit = 0, S.SPLICE_NOALLOC_WORKSPACE_BYTES
+    call = sp.make_call(0, 5, 0, 1.0)
+    for C, Hkv, G, D, Tp in itertools.product((5, 8, 64, 128, 256), (1, 8, 24), (1, 2, 4, 8), (64, 128, 256),
+                                              (400, 1000, 4096, 32768)):
+        sh = _shape(C, Hkv, G, D, Tp, "f32")
+        r = (ctypes.c_int64 * 4)()
+        plan.plan_bytes(ctypes.byref(sh), ctypes.byref(call), r)
+        assert r[0] == sp.splice_decode_attn_workspace_bytes(sh, call) <= sp.splice_decode_attn_workspace_bytes(sh)
+        assert (r[0] <= limit) == (r[1] <= limit), (C, Hkv, G, D, Tp, list(r))
+        if plan.takes_wide(ctypes.byref(sh), ctypes.byref(call)):
+            wide += 1
+            assert r[0] >= r[1] and 1 <= r[2] <= 16 and r[2] * r[3] >= Tp > (r[2] - 1) * r[3] and r[3] % 32 == 0
+    assert wide > 200, wide

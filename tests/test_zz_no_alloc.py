@@ -78,3 +78,20 @@ def test_more_pairs_after_fewer(dtype):
         q = workloads.make_q(w, 2, 9, device="cuda")
         (o_n, l_n), (o_w, l_w) = _pair(w, 2, 9, bufs, q, lw)
         assert np.array_equal(o_n, o_w) and np.array_equal(l_n, l_w), f"call {i}: noalloc bits differ"
+
+
+def test_f32_bits_at_the_array_limit():
+    """Many pairs and 4096 keys: 16 chunks would not fit the array, so both entries take fewer."""
+    w = workloads.get("qwen3-4b").with_(n_layers=4, n_q_heads=32, n_kv_heads=8, head_dim=128, prompt_len=4096,
+                                        span=(33, 4000), n_steps=10, donor=DONOR_BLANK, dtype="f32", scale=128 ** -0.5,
+                                        cells=tuple((i % 5, i % 3) for i in range(128)))
+    lw = workloads.cell_lw(w)
+    gc.announce("noalloc f32, 1024 pairs, 4096 keys")
+    bufs = gc.gpu_layer(w, 2)
+    q = workloads.make_q(w, 2, 9, device="cuda")
+    (o_n, l_n), (o_w, l_w) = _pair(w, 2, 9, bufs, q, lw)
+    assert np.array_equal(o_n, o_w) and np.array_equal(l_n, l_w)
+    rows = [(3, 0), (77, 31), (127, 13)]
+    ref_o, _ = gc.run_oracle(w, 2, 9, gc.host(bufs), workloads.to_numpy(q), lw, rows=rows)
+    for (c, h), ref in zip(rows, ref_o):
+        assert np.abs(o_n[c, h] - ref).max() <= 4e-6 * np.abs(ref).max()
