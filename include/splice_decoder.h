@@ -73,8 +73,10 @@ SPLICE_API int32_t splice_decoder_product(const void *x, const void *w, void *y,
  * logits [rows][vocab] = float(bf16(h . w [d][vocab])), bf16 inputs, h packed
  * (splice_decoder_norm), fp32 sums: 1..SPLICE_MAX_CELLS rows, d a multiple of
  * 32, vocab of 8.  scratch: splice_decoder_head_bytes bytes (may be 0) on the
- * current device.
+ * current device.  splice_decoder_head_takes: whether a pass uses it (1) or
+ * leaves the head to the library (0).
  */
+SPLICE_API int32_t splice_decoder_head_takes(int32_t rows, int32_t d, int32_t vocab);
 SPLICE_API int64_t splice_decoder_head_bytes(int32_t rows, int32_t d, int32_t vocab);
 SPLICE_API int32_t splice_decoder_head(const void *h, const void *w, float *logits, int32_t rows, int32_t d,
                                        int32_t vocab, void *scratch, size_t scratch_bytes, void *stream);

@@ -400,6 +400,22 @@ int32_t splice_decoder_product(const void *x, const void *w, void *y, int32_t ro
     return launched();
 }
 
+// The own head where it is the faster one (us, the library's product with its
+// conversion / this, some 25 of the former the host's): columns for three
+// quarters of the compute units (K = 4096, 128 rows: 49152 columns 96 / 81, but
+// 32000 62 / 73, 16384 43 / 69) and at most 128 rows, more read the weights again
+// (K = 4096, 151936 columns, 128 rows 313 / 240, 129 rows 333 / 444); with fewer
+// columns a work group's chain over K is what it takes, so K short for the rows
+// (16384 columns: 16 rows K = 4096 30 / 29, 5120 33 / 36; 64 rows K = 2048 28 / 29,
+// 2560 28 / 35; 128 rows K = 1024 27 / 23, 2048 29 / 39).
+int32_t splice_decoder_head_takes(int32_t rows, int32_t d, int32_t vocab) {
+    if (rows < 1 || rows > SPLICE_MAX_CELLS || d < 32 || d % 32 || d > 1 << 20 || vocab < 8 || vocab % 8 || vocab > 1 << 24)
+        return 0;
+    const int tiles = rows <= kHeadNarrowRows ? (vocab + 127) / 128 : (vocab + kHeadWide - 1) / kHeadWide;
+    if (4 * tiles >= 3 * compute_units()) return rows <= 128;
+    return d <= (rows <= kHeadNarrowRows ? 4096 : (rows <= 64 ? 2048 : 1024));
+}
+
 int64_t splice_decoder_head_bytes(int32_t rows, int32_t d, int32_t vocab) {
     if (rows < 1 || rows > SPLICE_MAX_CELLS || d < 32 || d % 32 || d > 1 << 20 || vocab < 8 || vocab % 8 ||
         vocab > 1 << 24)

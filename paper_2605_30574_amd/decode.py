@@ -50,7 +50,7 @@ def _library():
                            ("rope_table", [vp, vp, vp, i32, i32, i32, ctypes.c_double, vp]),
                            ("rope", [vp, vp, vp, i32, i32, i32, i32, vp]),
                            ("round", [vp, vp, i32, i32, i32, vp]),
-                           ("silu", [vp, vp, vp, i32, i32, i32, vp]), ("product_takes", [i32, i32, i32]),
+                           ("silu", [vp, vp, vp, i32, i32, i32, vp]), ("product_takes", [i32, i32, i32]), ("head_takes", [i32, i32, i32]),
                            ("product", [vp, vp, vp, i32, i32, i32, vp]),
                            ("head", [vp, vp, vp, i32, i32, i32, vp, ctypes.c_size_t, vp]), ("argmax", [vp, i32, i32, vp, vp, vp])):
             f = getattr(lib, "splice_decoder_" + name)
@@ -87,7 +87,8 @@ def _current(device) -> bool:
 def greedy(logits: torch.Tensor) -> torch.Tensor:
     """The lowest index of the largest logit of every row (int64)."""
     if not (type(logits) is torch.Tensor and _unwatched() and logits.is_cuda and _current(logits.device) and
-            logits.dim() == 2 and logits.is_contiguous() and logits.dtype == torch.float32 and 0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
+            logits.dim() == 2 and logits.is_contiguous() and logits.dtype == torch.float32 and
+            0 < logits.shape[0] <= 65535 and 0 < logits.shape[1] <= 1 << 24):
         return torch.argmax(logits, dim=-1)
     n, vocab = logits.shape
     tokens = torch.empty(n, dtype=torch.int64, device=logits.device)
@@ -176,8 +177,8 @@ class SweepDecoder:
         C, Hq, Hkv, D, dev, d = self.C, w.n_q_heads, w.n_kv_heads, w.head_dim, x.device, x.shape[-1]
         if torch.is_autocast_enabled("cuda") and torch.get_autocast_dtype("cuda") != torch.bfloat16:
             return False   # the products are another type's
-        if not (_unwatched() and x.is_cuda and _current(dev) and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and _dense(x) and
-                (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
+        if not (_unwatched() and x.is_cuda and _current(dev) and C > 0 and d % 8 == 0 and _plain(x, dev, C, d) and
+                _dense(x) and (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
             return False
         for p in wt["layers"]:
             F = p["w_gate"].shape[-1]
@@ -258,7 +259,7 @@ class SweepDecoder:
             delta = product(act.data_ptr(), p["w_down"]) if own_down else act @ p["w_down"]
         head = wt["lm_head"]
         vocab = head.shape[1]
-        own_head = _dense(head) and d % 32 == 0 and vocab % 8 == 0 and 0 < vocab <= 1 << 24
+        own_head = _dense(head) and lib.splice_decoder_head_takes(C, d, vocab) == 1
         norm(delta, wt["norm_f"], first, own_head)
         if not own_head:
             return (h @ head).float()

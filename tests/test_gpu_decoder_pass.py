@@ -78,6 +78,8 @@ def _compare(make, wt, tokens, steps, what, pos=None):
     (100, 1056, 64, 66600, 2, 1, 64, 1), (64, 2048, 256, 264, 32, 4, 64, 1), (128, 2056, 2176, 264, 16, 2, 128, 2), (9, 72, 104, 100, 4, 2, 64, 1),
     # the second layer's cache rows follow the first one's products: the query, output and down projections the
     # library's own kernel takes, and the 2048 columns at 128 rows it leaves
+    # more rows than one pass over the head's weights, and a long K for few columns: the library's head
+    (130, 256, 64, 49160, 2, 1, 64, 1), (20, 2304, 64, 264, 2, 1, 64, 1),
     (64, 2048, 2176, 264, 32, 4, 64, 2), (128, 2560, 2176, 264, 32, 8, 128, 2), (128, 2048, 2176, 264, 32, 4, 64, 2)])
 def test_fused_pass_keeps_the_bits(C, d, F, V, Hq, Hkv, D, N):
     make, wt, tokens, steps = _decoder(C, d, F, V, Hq, Hkv, D, N)
@@ -233,6 +235,15 @@ def test_add_norm_adds_as_the_mean(C, d):
             assert not got[C:].any()
     assert lib.splice_decoder_add_norm(x.data_ptr(), delta.data_ptr(), gain.data_ptr(), h.data_ptr(), None, C, 8200, 1e-6, 0,
                                        None) == sp.SPLICE_EUNSUPPORTED
+
+
+def test_head_takes():
+    takes = decode._library().splice_decoder_head_takes
+    for dims, want in (((128, 4096, 151936), 1), ((129, 4096, 151936), 0), ((128, 4096, 49152), 1), ((128, 4096, 32000), 0),
+                       ((16, 4096, 16384), 1), ((16, 5120, 16384), 0), ((64, 2048, 264), 1), ((64, 2080, 264), 0),
+                       ((128, 1024, 264), 1), ((128, 1056, 264), 0), ((200, 1024, 264), 1), ((8, 2560, 151936), 1),
+                       ((8, 2568, 151936), 0), ((8, 2560, 151940), 0)):
+        assert takes(*dims) == want, dims
 
 
 # one and several row groups, rows and columns that fill the last tile in part,
