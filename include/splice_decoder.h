@@ -34,8 +34,10 @@ SPLICE_API int32_t splice_decoder_norm(const float *x, const float *mean_sq, con
 
 /*
  * splice_decoder_residual, the mean of the squares and splice_decoder_norm at once, d at most
- * SPLICE_ADD_NORM_MAX_D: h plain, h_packed packed, either may be NULL.  The squares are added in the order in which PyTorch adds rows of 256 to 7680 values when
- * there are at least eight; for other sizes the mean is as accurate but may differ in its last bit.
+ * SPLICE_ADD_NORM_MAX_D: h plain, h_packed packed, either may be NULL.  The
+ * squares are added in the order in which PyTorch adds rows of 256 to 7680
+ * values when there are at least eight; for other sizes the mean is as accurate
+ * but may differ in its last bit.
  */
 #define SPLICE_ADD_NORM_MAX_D 8192
 SPLICE_API int32_t splice_decoder_add_norm(float *x, const void *delta, const void *gain, void *h, void *h_packed,
@@ -84,6 +86,7 @@ SPLICE_API int32_t splice_decoder_head(const void *h, const void *w, float *logi
 /*
  * tokens[r] = the lowest index of the largest of logits[r][0..vocab) (a NaN
  * counts as the largest).  scratch: rows * SPLICE_ARGMAX_PARTS * 8 bytes.
+ * logits aligned to 4 bytes, tokens and scratch to 8.
  */
 #define SPLICE_ARGMAX_PARTS 64
 SPLICE_API int32_t splice_decoder_argmax(const float *logits, int32_t rows, int32_t vocab, int64_t *tokens,

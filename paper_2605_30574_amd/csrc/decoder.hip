@@ -224,6 +224,11 @@ bool good(std::initializer_list<const void *> ptrs) {
     return true;
 }
 
+// [rows][d] as units of eight values, packed in steps of 32.
+bool good_rows(int32_t rows, int32_t d, int32_t packed) {
+    return rows >= 1 && d >= 8 && d % 8 == 0 && !(packed && d % 32) && (int64_t)rows * d <= kMostValues;
+}
+
 // How the columns of a head are spread: `n_full` whole tiles, the rest split
 // over K.  Tiles run in rounds of as many work groups as the GPU holds; a last
 // round that is at most half full takes as long as a full one, so its tiles
@@ -299,10 +304,9 @@ int32_t splice_decoder_residual(float *x, const void *delta, float *sq, int64_t 
 int32_t splice_decoder_norm(const float *x, const float *mean_sq, const void *gain, void *h, int32_t rows, int32_t d,
                             float eps, int32_t packed, void *stream) {
     if (!good({x, gain, h}) || !mean_sq || !splice::aligned(mean_sq, 4)) return SPLICE_EINVAL;
-    if (rows < 1 || d < 8 || d % 8 || (packed && d % 32)) return SPLICE_EUNSUPPORTED;
+    if (!good_rows(rows, d, packed)) return SPLICE_EUNSUPPORTED;
     hipLaunchKernelGGL(norm_kernel, dim3(blocks_of((int64_t)rows * (d / 8))), dim3(kDecThreads), 0, (hipStream_t)stream,
-                       x, mean_sq, (const __bf16 *)gain, (__bf16 *)h, rows, d, eps,
-                       packed);
+                       x, mean_sq, (const __bf16 *)gain, (__bf16 *)h, rows, d, eps, packed);
     return launched();
 }
 
@@ -339,15 +343,10 @@ int32_t splice_decoder_rope(void *q, void *k, const float *tab, int32_t rows, in
     return launched();
 }
 
-// [rows][d] as units of eight values, packed in steps of 32.
-static bool good_rows(int32_t rows, int32_t d, int32_t packed) {
-    return rows >= 1 && d >= 8 && d % 8 == 0 && !(packed && d % 32);
-}
-
 int32_t splice_decoder_round(const float *src, void *dst, int32_t rows, int32_t d, int32_t packed, void *stream) {
     if (!good({src, dst})) return SPLICE_EINVAL;
+    if (!good_rows(rows, d, packed)) return SPLICE_EUNSUPPORTED;
     const int64_t units = (int64_t)rows * (d / 8);
-    if (!good_rows(rows, d, packed) || units > kMostValues / 8) return SPLICE_EUNSUPPORTED;
     hipLaunchKernelGGL(round_kernel, dim3(blocks_of(units)), dim3(kDecThreads), 0, (hipStream_t)stream, src, (__bf16 *)dst,
                        units, rows, d, packed);
     return launched();
@@ -356,8 +355,8 @@ int32_t splice_decoder_round(const float *src, void *dst, int32_t rows, int32_t 
 int32_t splice_decoder_silu(const void *gate, const void *up, void *act, int32_t rows, int32_t d, int32_t packed,
                             void *stream) {
     if (!good({gate, up, act}) || (packed && (act == gate || act == up))) return SPLICE_EINVAL;
+    if (!good_rows(rows, d, packed)) return SPLICE_EUNSUPPORTED;
     const int64_t units = (int64_t)rows * (d / 8);
-    if (!good_rows(rows, d, packed) || units > kMostValues / 8) return SPLICE_EUNSUPPORTED;
     hipLaunchKernelGGL(silu_kernel, dim3(blocks_of(units)), dim3(kDecThreads), 0, (hipStream_t)stream,
                        (const __bf16 *)gate, (const __bf16 *)up, (__bf16 *)act, units, rows, d, packed);
     return launched();
@@ -445,7 +444,9 @@ int32_t splice_decoder_head(const void *h, const void *w, float *logits, int32_t
 
 int32_t splice_decoder_argmax(const float *logits, int32_t rows, int32_t vocab, int64_t *tokens, void *scratch,
                               void *stream) {
-    if (!logits || !tokens || !scratch) return SPLICE_EINVAL;
+    if (!logits || !tokens || !scratch || !splice::aligned(logits, 4) || !splice::aligned(tokens, 8) ||
+        !splice::aligned(scratch, 8))
+        return SPLICE_EINVAL;
     if (rows < 1 || rows > 65535 || vocab < 1 || vocab > 1 << 24) return SPLICE_EUNSUPPORTED;
     // about eight work groups a compute unit, each with a thousand values or more
     int parts = (2048 + rows - 1) / rows;

@@ -251,3 +251,16 @@ def test_noalloc_rejects_calls_beyond_its_array_before_device_access():
     bad = sp.make_call(0, 0, 0, float("nan"))
     assert lib.splice_decode_attn_noalloc(ctypes.byref(sh), ctypes.byref(bad), lw, *([fake] * 9), None) == \
         sp.SPLICE_EINVAL
+
+
+def test_decoder_entries_refuse_before_device_access():
+    """Sizes beyond a grid and misaligned pointers of the decode pass's kernels."""
+    from paper_2605_30574_amd import decode
+    lib = decode._library()
+    p, odd = 0x1000, 0x1004   # never dereferenced
+    assert lib.splice_decoder_norm(p, p, p, p, 2 ** 31 - 1, 2 ** 31 - 8, 1e-6, 0, None) == sp.SPLICE_EUNSUPPORTED
+    assert lib.splice_decoder_round(p, p, 2 ** 31 - 1, 2 ** 31 - 8, 0, None) == sp.SPLICE_EUNSUPPORTED
+    assert lib.splice_decoder_norm(p, p, p, odd, 1, 8, 1e-6, 0, None) == sp.SPLICE_EINVAL
+    assert lib.splice_decoder_argmax(p, 1, 8, odd, p, None) == sp.SPLICE_EINVAL
+    assert lib.splice_decoder_argmax(p, 1, 8, p, odd, None) == sp.SPLICE_EINVAL
+    assert lib.splice_decoder_argmax(0x1002, 1, 8, p, p, None) == sp.SPLICE_EINVAL
