@@ -887,10 +887,12 @@ __device__ int fused_prompt_item(const AttnArgs &a, int item, char *lds, int *s_
 //
 // With more than 8 slots the rows' records (m, l, w) would not fit beside the
 // outputs in registers: each is loaded once by the work group and read from
-// LDS.  The chain of sc1 round trips bounds it; against loading four outputs
-// and a record a slot per thread, at 16 slots: 4 cells, 4096 keys 24.4 -> 19.5
-// us a call, 16 cells, 8192 keys 30.5 -> 26.3, D = 256, 48 cells, 4096 keys
-// 29.8 -> 24.9.
+// LDS.  The chain of sc1 round trips bounds it.  Against loading four outputs
+// and a record a slot per thread, at 16 slots (us a call, 61 generated rows,
+// 4096 keys unless named): D = 128, G = 4, 8 KV heads, 4 cells 22.3 -> 18.0, 16
+// cells 23.6 -> 19.3, of 8192 keys 30.9 -> 26.3; D = 256, G = 2, 4 KV heads, 48
+// cells 29.5 -> 24.8 (101 rows: 27.2 -> 25.7); D = 256, G = 8, 1 KV head, 18
+// cells 42.9 -> 25.0.
 template <int D, int G, int NW, int B, int U>
 __device__ __forceinline__ void gen_merge_in_place(const AttnArgs &a, const WaveState<D> &S, char *buf, int wpp,
                                                    int n_pairs, int c0, int g) {

@@ -27,7 +27,6 @@ __global__ __launch_bounds__(DirectWaves<D>::NT) void direct_kernel(AttnArgs a) 
     using W = WaveMfma<D>;
     constexpr int NW = DirectWaves<D>::NW, NT = DirectWaves<D>::NT, NSEG = 5;
     __shared__ __attribute__((aligned(16))) char lds[cmax(NW * W::LDS, NW * G * (D + 2) * 4)];
-    if (threadIdx.x == 0) trunk_written() = 0;
     const int g = blockIdx.x % a.Hkv, c = a.gorder[blockIdx.x / a.Hkv];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = threadIdx.x & 15;
     bf16x8_t qb[W::NDS];

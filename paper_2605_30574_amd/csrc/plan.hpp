@@ -513,7 +513,13 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
 // of 189 12.8 / 12.6; 640 pairs of 38 keys 11.1 / 9.6, of 93 11.8 / 11.8.
 // D = 64 321 keys 12.3 / 10.2, 711 keys 9.8 / 12.4; 400 pairs of 211 keys
 // 11.4 / 10.2, of 321 12.5 / 12.3.  D = 256 211 keys 12.8 / 12.1, 321 keys
-// 13.9 / 15.3; 320 pairs of 51 keys 13.0 / 10.6, of 161 16.5 / 19.1.
+// 13.9 / 15.3; 320 pairs of 51 keys 13.0 / 10.6, of 161 16.5 / 19.1.  They hold
+// at every group size: at the limits themselves, G = 1 and G = 8, D = 128 384
+// keys 15.3 / 11.5 (88 pairs) and 14.2 / 12.3 (228 pairs), 160 keys 15.3 / 12.0
+// and 14.7 / 12.4, 64 keys 10.6 / 10.4 and 12.9 / 11.4; D = 64 10.2 / 8.9 and
+// 10.0 / 9.4, 15.6 / 10.8 and 16.4 / 11.1, 9.7 / 8.1 and 11.8 / 9.0; D = 256
+// 13.8 / 12.6 and 16.8 / 13.3, 18.8 / 14.0 and 18.8 / 16.9.  Of 132 random calls
+// below the limits, 1 to 8 KV heads, none was slower (mean 1.32).
 inline bool direct_bf16(const splice_shape &sh, int n_vis, int n_active, int n_cu) {
     if (!bf16_path(sh) || n_active <= 0 || n_cu <= 0) return false;
     const int per_cu = ceil_div((int64_t)n_active * sh.n_kv_heads, n_cu);

@@ -18,8 +18,8 @@
 // cells is what bounds them (64 cells, 1024 keys: 0.5 GB of L2 reads a call);
 // here the fp32 products bound the prompt items (12 us a 1024 keys at 64 cells,
 // 8 KV heads, G = 4, D = 128; the products' peak allows 8.5) and run beside the
-// generated rows' reads.  Measured there, 129 generated rows: 1024 keys 75.5 ->
-// 37.7 us a call, 2048 keys 113.6 -> 49; 16 cells and 1024 keys 33.6 -> 21.7.
+// generated rows' reads.  Measured there, 129 generated rows: 1024 keys 75.0 ->
+// 38.1 us a call, 2048 keys 113.9 -> 51.3; 16 cells and 1024 keys 32.1 -> 21.2.
 // The second launch costs less than counting arrivals and merging in the last
 // item to finish (1024 keys: 41 us against 56), and all partials are stored
 // plainly.  Sums are kept in short chains (see WideF), so that the error against
