@@ -277,6 +277,7 @@ constexpr int kWideF32Items = 256;               // prompt work groups aimed for
 constexpr int kWideF32Chunk = 64;                // keys of a chunk, at least
 constexpr int kWideF32LongChunk = 256;           // ... and at most, up to kWideF32MaxChunks chunks
 constexpr int kWideF32MaxChunks = 16;
+
 inline int wide_f32_chunk_target(const splice_shape &sh) {
     const int groups = sh.n_kv_heads * (ceil_div((int64_t)sh.n_cells * group_of(sh), group_rows(sh.head_dim)) + 1);
     const int t = kWideF32Items / groups;
