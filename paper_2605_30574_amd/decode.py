@@ -72,7 +72,12 @@ def _unwatched() -> bool:
 def _plain(t, device, *shape) -> bool:
     """A bf16 matrix of this shape on the device that autograd does not follow (any strides)."""
     return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == torch.bfloat16 and t.device == device and
-            tuple(t.shape) == shape and not (t.requires_grad and torch.is_grad_enabled()))
+            t.layout == torch.strided and tuple(t.shape) == shape and not (t.requires_grad and torch.is_grad_enabled()))
+
+
+def _columns(t) -> int:
+    """Columns of a weight that is a matrix, else 0 (an object that only knows how to be multiplied, say)."""
+    return t.shape[1] if isinstance(t, torch.Tensor) and t.dim() == 2 else 0
 
 
 def _dense(t) -> bool:
@@ -181,7 +186,7 @@ class SweepDecoder:
                 _dense(x) and (pos is None or (pos.device == dev and tuple(pos.shape) == (C,)))):
             return False
         for p in wt["layers"]:
-            F = p["w_gate"].shape[-1]
+            F = _columns(p["w_gate"])
             if not (F % 8 == 0 and F > 0 and _plain(p["w_gate"], dev, d, F) and _plain(p["w_up"], dev, d, F) and
                     _plain(p["w_down"], dev, F, d) and _plain(p["w_q"], dev, d, Hq * D) and
                     _plain(p["w_k"], dev, d, Hkv * D) and _plain(p["w_v"], dev, d, Hkv * D) and
@@ -189,8 +194,7 @@ class SweepDecoder:
                     _plain(p["norm_2"], dev, d) and _dense(p["norm_2"])):
                 return False
         head = wt["lm_head"]
-        return (_plain(wt["norm_f"], dev, d) and _dense(wt["norm_f"]) and head.dim() == 2 and
-                _plain(head, dev, d, head.shape[1]))
+        return _plain(wt["norm_f"], dev, d) and _dense(wt["norm_f"]) and _plain(head, dev, d, _columns(head))
 
     def _forward_fused(self, delta: torch.Tensor, steps, pos: Optional[torch.Tensor]) -> torch.Tensor:
         """forward() with the library's kernels between the products: the same roundings, so the same bits up to the head."""

@@ -117,6 +117,27 @@ def test_overridden_positions_are_used():
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
 
 
+class _Product:
+    """A weight that is no tensor: h @ weight is all it knows."""
+
+    def __init__(self, w):
+        self.w = w
+
+    def __rmatmul__(self, h):
+        return h @ self.w
+
+
+def test_weights_that_only_multiply():
+    make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
+    want = make(False).forward(tokens, steps)
+    for owner, name in ((wt["layers"][0], "w_gate"), (wt["layers"][0], "w_q"), (wt, "lm_head")):
+        keep, owner[name] = owner[name], _Product(owner[name])
+        gc.announce(f"decoder pass, {name} an object")
+        got = make(True).forward(tokens, steps)
+        owner[name] = keep
+        assert torch.equal(got, want), name
+
+
 def test_another_current_device_keeps_the_operations(monkeypatch):
     make, wt, tokens, steps = _decoder(5, 96, 160, 136, 4, 2, 64, 1)
     x = wt["embed"][tokens]
