@@ -153,7 +153,8 @@ SPLICE_API int64_t splice_decode_attn_workspace_bytes(const splice_shape *shape,
  * (cell, KV head) pairs need no re-initialisation.  The partial results lie
  * right behind the counters of a call's n_cells * n_kv_heads pairs, so a
  * workspace that is to serve another number of pairs is initialised again
- * first (its counters lie where a call with fewer left partial results).
+ * first (its counters lie where a call with fewer left partial results; f32
+ * calls that keep no counters leave theirs beyond any cell count's).
  * workspace must be 256-byte aligned and workspace_bytes a multiple of 4.
  */
 SPLICE_API int32_t splice_workspace_init(void *workspace, size_t workspace_bytes, void *stream);

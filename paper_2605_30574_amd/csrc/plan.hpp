@@ -228,6 +228,41 @@ inline void cut(int n, int target, int split, int *k, int *len, int min_chunk = 
     *k = ceil_div(n, *len);
 }
 
+struct WorkspaceLayout {
+    size_t stats_off;   // kStatsBytes of statistics (the hand-over count), kept across calls
+    size_t counters_off, counters_bytes;
+    size_t part_off, part_bytes;
+    size_t total;
+};
+
+// Statistics words at the start of a workspace (int32): [0] the number of
+// (cell, KV head) merges handed over by a generated-row item whose bounded
+// wait ran out, counted since splice_workspace_init.
+constexpr size_t kStatsBytes = 256;
+
+// Statistics, counters [C][Hkv] (int32), then the partial results: one
+// slot per (cell, KV head, chunk) -- for bf16 inputs the 16-bit prompt slots
+// [C][Hkv][n_slots - 1] followed by the fp32 generated-row slots [C][Hkv]
+// (one each), otherwise fp32 slots.  The f32 shared-prompt route (wide) counts
+// nothing; its slots start behind the counters of as many cells as a shape can
+// have, so calls of any number of cells may follow it in one workspace, as they
+// may follow the cellwise route it takes the place of.
+inline WorkspaceLayout workspace_layout(const splice_shape &sh, int n_slots, bool wide = false) {
+    WorkspaceLayout w;
+    const int64_t pairs = (int64_t)sh.n_cells * sh.n_kv_heads;
+    w.stats_off = 0;
+    w.counters_off = kStatsBytes;
+    w.counters_bytes = (size_t)round_up((wide ? (int64_t)SPLICE_MAX_CELLS * sh.n_kv_heads : pairs) * 4, 256);
+    w.part_off = w.counters_off + w.counters_bytes;
+    const size_t f32_slot = (size_t)slot_floats(group_of(sh), sh.head_dim) * 4;
+    w.part_bytes = bf16_path(sh) && n_slots > 0
+                       ? (size_t)pairs * ((size_t)(n_slots - 1) * (size_t)prompt_slot_bytes(sh) + f32_slot)
+                       : (size_t)pairs * (size_t)n_slots * f32_slot;
+    w.total = w.part_off + w.part_bytes;
+    if (w.total < 256) w.total = 256;
+    return w;
+}
+
 // f32 prompts up to this many visible keys take the cellwise path: each
 // (cell, KV head) streams its own list, re-reading the shared prompt from L2,
 // which costs less than the split and merge of the item path.
@@ -290,7 +325,7 @@ inline int wide_f32_chunk_target(const splice_shape &sh) {
 inline int wide_f32_chunk_cap(const splice_shape &sh) {
     const int64_t pairs = (int64_t)sh.n_cells * sh.n_kv_heads;
     const int64_t slot = (int64_t)slot_floats(group_of(sh), sh.head_dim) * 4;
-    const int64_t room = (int64_t)SPLICE_NOALLOC_WORKSPACE_BYTES - 512 - 4 * pairs;   // statistics, counters
+    const int64_t room = (int64_t)(SPLICE_NOALLOC_WORKSPACE_BYTES - workspace_layout(sh, 0, true).part_off);
     const int64_t cap = pairs > 0 && room > 0 ? room / (pairs * slot) - 1 : 0;
     return cap < 0 ? 0 : (cap < kWideF32MaxChunks ? (int)cap : kWideF32MaxChunks);
 }
@@ -315,6 +350,7 @@ struct AttnPlan {
     int n_p, p_len;          // prompt chunks over the visible prompt
     int n_g, g_len;          // chunks over the visible generated rows
     int n_slots;             // partial results per (cell, KV head)
+    size_t bytes;            // workspace the call asks for
     int n_prompt_items, n_gen_items;
     int gen_pairs;           // bf16: (cell, KV head) pairs per generated-row work group
 };
@@ -421,9 +457,11 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
             p.cellwise = false;
             p.n_g = 1;
             p.g_len = geo.n_gen;
+            p.n_slots = p.n_p + 1;
             // a call asks for no less than it would without this route
-            const int general = plan_from_geo(sh, call, geo, n_clean, n_active, res, same_rows, false).n_slots;
-            p.n_slots = p.n_p + 1 > general ? p.n_p + 1 : general;
+            const size_t general = plan_from_geo(sh, call, geo, n_clean, n_active, res, same_rows, false).bytes;
+            p.bytes = workspace_layout(sh, p.n_slots, true).total;
+            if (p.bytes < general) p.bytes = general;
             p.n_prompt_items = kXcds * row_groups(sh, n_clean, n_active) * ceil_div((int64_t)sh.n_kv_heads * p.n_p, kXcds);
             p.n_gen_items = sh.n_cells * sh.n_kv_heads;
             p.gen_pairs = 1;
@@ -435,6 +473,7 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
         p.n_p = p.n_g = 0;
         p.p_len = p.g_len = 64;
         p.n_slots = 0;
+        p.bytes = workspace_layout(sh, 0).total;
         p.n_prompt_items = p.n_gen_items = 0;
         p.gen_pairs = 1;
         return p;
@@ -478,6 +517,7 @@ inline AttnPlan plan_from_geo(const splice_shape &sh, const splice_call &call, c
         cut(p.geo.n_gen, gen_chunk_target(sh), call.split_keys, &p.n_g, &p.g_len);
     }
     p.n_slots = p.n_p + p.n_g;
+    p.bytes = workspace_layout(sh, p.n_slots).total;
     if (bf16_path(sh)) {
         // units (KV head, chunk) padded to whole rounds of kXcds, times row groups
         p.n_prompt_items = p.n_p > 0 ? kXcds * row_groups(sh, n_clean, n_active) *
@@ -544,38 +584,6 @@ inline bool gen_v_nontemporal(const splice_shape &sh, int n_gen) {
     return bytes > kGenNtPromptBytes || n_gen >= kGenNtRows;
 }
 
-struct WorkspaceLayout {
-    size_t stats_off;   // kStatsBytes of statistics (the hand-over count), kept across calls
-    size_t counters_off, counters_bytes;
-    size_t part_off, part_bytes;
-    size_t total;
-};
-
-// Statistics words at the start of a workspace (int32): [0] the number of
-// (cell, KV head) merges handed over by a generated-row item whose bounded
-// wait ran out, counted since splice_workspace_init.
-constexpr size_t kStatsBytes = 256;
-
-// Statistics, counters [C][Hkv] (int32), then the partial results: one
-// slot per (cell, KV head, chunk) -- for bf16 inputs the 16-bit prompt slots
-// [C][Hkv][n_slots - 1] followed by the fp32 generated-row slots [C][Hkv]
-// (one each), otherwise fp32 slots.
-inline WorkspaceLayout workspace_layout(const splice_shape &sh, int n_slots) {
-    WorkspaceLayout w;
-    const int64_t pairs = (int64_t)sh.n_cells * sh.n_kv_heads;
-    w.stats_off = 0;
-    w.counters_off = kStatsBytes;
-    w.counters_bytes = (size_t)round_up(pairs * 4, 256);
-    w.part_off = w.counters_off + w.counters_bytes;
-    const size_t f32_slot = (size_t)slot_floats(group_of(sh), sh.head_dim) * 4;
-    w.part_bytes = bf16_path(sh) && n_slots > 0
-                       ? (size_t)pairs * ((size_t)(n_slots - 1) * (size_t)prompt_slot_bytes(sh) + f32_slot)
-                       : (size_t)pairs * (size_t)n_slots * f32_slot;
-    w.total = w.part_off + w.part_bytes;
-    if (w.total < 256) w.total = 256;
-    return w;
-}
-
 // The no-allocation entry's array, which serves calls of every shape in turn:
 // as a workspace of SPLICE_NOALLOC_WORKSPACE_BYTES, but with a counter block of
 // one size, so that no shape's partial results lie where another shape keeps
@@ -594,7 +602,7 @@ inline WorkspaceLayout noalloc_layout(const splice_shape &sh, int n_slots) {
     return w;
 }
 
-// Most slots any default-split call on this shape uses.  For n keys the
+// Most workspace any default-split call on this shape asks for.  For n keys the
 // default cut makes at most min(ceil(n / kMinChunk), target) chunks (each
 // chunk is at least n / that many keys long), and that bound grows with n;
 // a call sees at most T_p prompt keys and gen_capacity generated rows.
@@ -604,19 +612,18 @@ inline int max_default_chunks(int n, int target, int min_chunk = kMinChunk) {
     return k < target ? k : target;
 }
 
-inline int worst_default_slots(const splice_shape &sh) {
+inline size_t worst_default_bytes(const splice_shape &sh) {
     // bf16: a decode step with one active cell takes the most chunks
     const int prompt = max_default_chunks(sh.prompt_len, prompt_chunk_target(sh, bf16_path(sh) ? 1 : sh.n_cells),
                                           bf16_path(sh) ? kWideMinChunk : kMinChunk);
-    if (bf16_path(sh)) return prompt + 1;
-    const int items = prompt + max_default_chunks(sh.gen_capacity, gen_chunk_target(sh));
+    if (bf16_path(sh)) return workspace_layout(sh, prompt + 1).total;
+    const size_t items = workspace_layout(sh, prompt + max_default_chunks(sh.gen_capacity, gen_chunk_target(sh))).total;
     // a window may leave fewer keys: the shared-prompt rule holds at some number
     // of keys up to prompt_len if at that, or at the most "short" ones
     const int cap = wide_f32_chunk_cap(sh);
     const int few = sh.prompt_len < kWideF32ShortKeys ? sh.prompt_len : kWideF32ShortKeys;
-    const int wide = wide_f32(sh, sh.prompt_len, cap) || wide_f32(sh, few, cap)
-                         ? max_default_chunks(sh.prompt_len, cap, kWideF32Chunk) + 1
-                         : 0;
+    if (!wide_f32(sh, sh.prompt_len, cap) && !wide_f32(sh, few, cap)) return items;
+    const size_t wide = workspace_layout(sh, max_default_chunks(sh.prompt_len, cap, kWideF32Chunk) + 1, true).total;
     return items > wide ? items : wide;
 }
 

@@ -173,23 +173,19 @@ splice::Residency residency(const void *kernel, int threads) {
 int64_t attn_workspace_bytes(const splice_shape *shape, const splice_call *call, bool every_count) {
     int32_t rc = splice::validate_shape(shape);
     if (rc != SPLICE_OK) return rc;
-    int n_slots;
-    if (call) {
-        rc = splice::validate_call(*shape, call);
-        if (rc != SPLICE_OK) return rc;
-        const splice::Geometry geo = splice::geometry(*shape, *call);
-        const int n_hi = shape->n_cells > 0 ? shape->n_cells : 1;
-        const int n_lo = every_count && call->split_keys == 0 ? 1 : n_hi;
-        n_slots = 0;
-        for (int n = n_lo; n <= n_hi; ++n) {   // the slots do not depend on the cell split
-            const int k = splice::plan_from_geo(*shape, *call, geo, 0, n).n_slots;
-            n_slots = k > n_slots ? k : n_slots;
-        }
-        if (n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
-    } else {
-        n_slots = splice::worst_default_slots(*shape);
+    if (!call) return (int64_t)splice::worst_default_bytes(*shape);
+    rc = splice::validate_call(*shape, call);
+    if (rc != SPLICE_OK) return rc;
+    const splice::Geometry geo = splice::geometry(*shape, *call);
+    const int n_hi = shape->n_cells > 0 ? shape->n_cells : 1;
+    const int n_lo = every_count && call->split_keys == 0 ? 1 : n_hi;
+    size_t bytes = 0;
+    for (int n = n_lo; n <= n_hi; ++n) {   // the slots do not depend on the cell split
+        const splice::AttnPlan p = splice::plan_from_geo(*shape, *call, geo, 0, n);
+        if (p.n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
+        bytes = p.bytes > bytes ? p.bytes : bytes;
     }
-    return (int64_t)splice::workspace_layout(*shape, n_slots).total;
+    return (int64_t)bytes;
 }
 
 int32_t launch_status() {
@@ -390,9 +386,9 @@ int32_t decode_attn_impl(const splice_shape *shape, const splice_call *call, con
         splice::plan_from_geo(sh, hi_call, geo, n_clean, n_active, res, g_lo.n_gen == g_hi.n_gen);
     if (plan.n_slots > splice::kMaxSlots) return SPLICE_EUNSUPPORTED;
     const splice::WorkspaceLayout wl =
-        noalloc ? splice::noalloc_layout(sh, plan.n_slots) : splice::workspace_layout(sh, plan.n_slots);
+        noalloc ? splice::noalloc_layout(sh, plan.n_slots) : splice::workspace_layout(sh, plan.n_slots, plan.wide);
     if (!workspace || !splice::aligned(workspace, 256)) return SPLICE_EWORKSPACE;
-    if (workspace_bytes < wl.total) return SPLICE_EWORKSPACE;
+    if (workspace_bytes < (noalloc ? wl.total : plan.bytes)) return SPLICE_EWORKSPACE;
 
     AttnArgs a;
     a.q = (const char *)q;

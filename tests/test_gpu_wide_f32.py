@@ -138,3 +138,21 @@ def test_error_is_not_above_the_general_routes(C, Hq, Hkv, D, Tp):
     err, err_g = (float(np.linalg.norm(x - ref)) for x in (out, general))
     assert err <= 1.1 * err_g, (err / np.linalg.norm(ref), err_g / np.linalg.norm(ref))
     assert np.abs(out - ref).max() <= 4e-6 * np.abs(ref).max()
+
+
+def test_a_workspace_shared_with_more_cells():
+    """The route keeps no counters and leaves its partial results behind those of
+    any cell count: a bf16 call with more cells may follow in the same workspace."""
+    few = _w(64, 32, 8, 128, 400, (40, 380), DONOR_BLANK)
+    many = few.with_(cells=tuple((i % 5, i % 3) for i in range(128)), prompt_len=1100, span=(40, 1000), dtype="bf16")
+    need = [sp.splice_decode_attn_workspace_bytes(gc.shape_of(w), sp.make_call(2, 5, 0, w.scale)) for w in (few, many)]
+    ws = torch.empty(max(need), dtype=torch.uint8, device="cuda")
+    sp.splice_workspace_init(ws)
+    for w in (few, many):
+        lw = workloads.cell_lw(w)
+        bufs = gc.gpu_layer(w, 2)
+        q = workloads.make_q(w, 2, 5, device="cuda")
+        gc.announce(f"shared workspace {w.dtype} {w.n_cells} cells")
+        o, l = gc.run_attn(w, 2, 5, bufs, q, lw, ws=ws)
+        o2, l2 = gc.run_attn(w, 2, 5, bufs, q, lw)
+        assert np.array_equal(o, o2) and np.array_equal(l, l2), w.dtype

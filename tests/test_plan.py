@@ -20,7 +20,7 @@ int noalloc_ranges(const splice_shape *sh, const splice_call *call, int64_t *r) 
     if (validate_shape(sh) != SPLICE_OK || validate_call(*sh, call) != SPLICE_OK) return 0;
     const Geometry geo = geometry(*sh, *call);
     const AttnPlan p = plan_from_geo(*sh, *call, geo, sh->n_cells / 2, sh->n_cells);
-    if (p.n_slots < 1 || workspace_layout(*sh, p.n_slots).total > SPLICE_NOALLOC_WORKSPACE_BYTES) return 0;
+    if (p.n_slots < 1 || p.bytes > SPLICE_NOALLOC_WORKSPACE_BYTES) return 0;
     const WorkspaceLayout w = noalloc_layout(*sh, p.n_slots);
     r[0] = w.counters_off; r[1] = r[0] + (int64_t)sh->n_cells * sh->n_kv_heads * 4;
     r[2] = w.part_off; r[3] = r[2] + w.part_bytes; r[4] = kNoallocBytes;
@@ -30,13 +30,15 @@ int noalloc_ranges(const splice_shape *sh, const splice_call *call, int64_t *r) 
 int takes_wide(const splice_shape *sh, const splice_call *call) {
     return plan_from_geo(*sh, *call, geometry(*sh, *call), sh->n_cells / 2, sh->n_cells).wide;
 }
-// workspace bytes of the call's plan [0] and of the plan without that route [1], chunks [2] and their length [3]
+// workspace bytes of the call's plan [0] and of the plan without that route [1], chunks [2] and their length [3], where
+// its partial results lie [4, 5)
 void plan_bytes(const splice_shape *sh, const splice_call *call, int64_t *r) {
     const Geometry geo = geometry(*sh, *call);
     const AttnPlan p = plan_from_geo(*sh, *call, geo, 0, sh->n_cells);
     const AttnPlan q = plan_from_geo(*sh, *call, geo, 0, sh->n_cells, Residency(), true, false);
-    r[0] = workspace_layout(*sh, p.n_slots).total; r[1] = workspace_layout(*sh, q.n_slots).total;
-    r[2] = p.n_p; r[3] = p.p_len;
+    r[0] = p.bytes; r[1] = q.bytes; r[2] = p.n_p; r[3] = p.p_len;
+    const WorkspaceLayout w = workspace_layout(*sh, p.n_slots, p.wide);
+    r[4] = w.part_off; r[5] = w.total;
 }
 }
 """
@@ -94,11 +96,12 @@ def test_both_entries_take_one_f32_plan(plan):
     for C, Hkv, G, D, Tp in itertools.product((5, 8, 64, 128, 256), (1, 8, 24), (1, 2, 4, 8), (64, 128, 256),
                                               (400, 1000, 4096, 32768)):
         sh = _shape(C, Hkv, G, D, Tp, "f32")
-        r = (ctypes.c_int64 * 4)()
+        r = (ctypes.c_int64 * 6)()
         plan.plan_bytes(ctypes.byref(sh), ctypes.byref(call), r)
         assert r[0] == sp.splice_decode_attn_workspace_bytes(sh, call) <= sp.splice_decode_attn_workspace_bytes(sh)
         assert (r[0] <= limit) == (r[1] <= limit), (C, Hkv, G, D, Tp, list(r))
         if plan.takes_wide(ctypes.byref(sh), ctypes.byref(call)):
             wide += 1
-            assert r[0] >= r[1] and 1 <= r[2] <= 16 and r[2] * r[3] >= Tp > (r[2] - 1) * r[3] and r[3] % 32 == 0
+            assert r[0] >= max(r[1], r[5]) and r[4] >= 256 + 4 * 256 * Hkv   # behind any cell count's counters
+            assert 1 <= r[2] <= 16 and r[2] * r[3] >= Tp > (r[2] - 1) * r[3] and r[3] % 32 == 0
     assert wide > 200, wide
